@@ -173,12 +173,17 @@ __device__ inline bool combine_on_surface(const T pf[6], const T cf[21], const T
 
 // The backward prediction at an entry, turned outward (phi - pi, pi - theta;
 // the theta terms of the covariance change sign), stored in the smoothed-state
-// arrays as propagate() hands it over, before the layer's material.
+// arrays as the propagation hands it over, before the layer's material.
 template <typename T>
 struct StorePrediction {
   T* so;
   T* co;
   int64_t os;
+  KF_HD void operator()(const SurfState<T>& s) const {
+    T c[21];
+    expand_cov(s, c);
+    (*this)(s.p, c);
+  }
   KF_HD void operator()(const T* p, const T* c) const {
 #pragma unroll
     for (int i = 0; i < 4; ++i) so[i * os] = p[i];
@@ -188,59 +193,6 @@ struct StorePrediction {
     for (int i = 0; i < 21; ++i) co[i * os] = (i >= 15 && i < 20) ? -c[i] : c[i];
   }
 };
-
-// One step of the smoothing backward pass (backward index k >= 1, entry r of
-// the track): the step of the plain backward pass, with the backward
-// prediction stored on the way (the combination with the forward filtered
-// state is a separate, entry-parallel pass: smooth_combine_kernel).  The rest
-// as in fit_entry (layer check, backup, roll-back of a non-finite step).
-template <typename T>
-__device__ inline bool smooth_step(const BwdArgs<T>& b, const TrackGeom<T>& g, int64_t t, int k, int r, int lay,
-                                   int& prev, bool valid, const T m[3], const T V[6], T p[6], T c[21], int& q,
-                                   uint32_t& st, T& chi2, int& nval, T* bk, int bk_stride) {
-  const FitArgs<T>& a = b.f;
-  if (lay < 0 || lay >= g.n_layers) {
-    st |= TRK_BAD_INPUT;
-    return false;
-  }
-#pragma unroll
-  for (int i = 0; i < 6; ++i) bk[i * bk_stride] = p[i];
-#pragma unroll
-  for (int i = 0; i < 21; ++i) bk[(6 + i) * bk_stride] = c[i];
-  const int qq = q;
-  uint32_t sst = 0;
-  const int kind = g.kind[lay];
-  const int64_t at = int64_t(r) * a.ld + t;
-  const StorePrediction<T> store{b.smooth_state + at, b.smooth_cov + at, a.ld * int64_t(a.max_len)};
-  if (k == 0) {
-    add_material_here(p, c, kind, g.x0[lay], g.mass, sst);   // the first entry: its prediction is the input
-  } else if (!propagate(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst,
-                        static_cast<T*>(nullptr), static_cast<PropTape<T>*>(nullptr), store)) {
-    st |= sst;
-    return false;
-  }
-  T c2 = T(0);
-  if (valid) {
-    T mm[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) mm[i] = m[i];
-    update(p, c, q, mm, V, c2, sst);
-  }
-  if (!all_finite(p, c, c2)) {
-    st |= sst | TRK_NONFINITE;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) p[i] = bk[i * bk_stride];
-#pragma unroll
-    for (int i = 0; i < 21; ++i) c[i] = bk[(6 + i) * bk_stride];
-    q = qq;
-    return false;
-  }
-  st |= sst;
-  chi2 += c2;
-  nval += valid ? 1 : 0;
-  prev = lay;
-  return true;
-}
 
 // Smoothing, entry-parallel: thread (r, t) combines the backward prediction
 // stored at entry r of track t with the forward filtered state of that entry
@@ -308,11 +260,12 @@ __device__ void backward_wave_staged(const BwdArgs<T>& b, const TrackGeom<T>& g,
   const bool in_range = t < a.n;
   int64_t last = 0;
   int len = 0, n_e = 0, k0 = 0;
-  T p[6], c[21];
-  int q = 0;
-  uint32_t st = 0;
+  FitState<T> f;
+  f.st = 0;
   bool run = false;
   if (in_range) {
+    T p[6], c[21];
+    int q;
     const int64_t e0 = a.hit_offsets[t];
     n_e = int(a.hit_offsets[t + 1] - e0);
     if (n_e > a.max_len) n_e = a.max_len;
@@ -344,14 +297,13 @@ __device__ void backward_wave_staged(const BwdArgs<T>& b, const TrackGeom<T>& g,
       if (ll >= 0 && ll < g.n_layers) impose_surface(c, p, g.kind[ll], g.pos[ll]);
       reverse_direction(p, c, q);
     } else {
-      st = TRK_BAD_INPUT;   // not refitted: the input is returned
+      f.st = TRK_BAD_INPUT;   // not refitted: the input is returned
     }
+    start_state(f, bk, bk_stride, p, c, q);
   }
   sb.e0[lane] = last;
   sb.len[lane] = len;
   const int kmax = wave_max(len);
-  T chi2 = T(0);
-  int nval = 0, prev = 0;
   bool live = run;
   const int64_t nh = a.n_hits;
   wave_sync();
@@ -390,32 +342,36 @@ __device__ void backward_wave_staged(const BwdArgs<T>& b, const TrackGeom<T>& g,
       const int32_t lv = sb.lv[jj][lane];
       const bool valid = (lv >> 16) != 0;
       const int lay = int16_t(lv & 0xffff);
-      if (k == 0) prev = lay;
       T m[3], V[6];
 #pragma unroll
       for (int x = 0; x < 3; ++x) m[x] = sb.v[x][jj][lane];
 #pragma unroll
       for (int x = 0; x < 6; ++x) V[x] = sb.v[3 + x][jj][lane];
       const int r = n_e - 1 - k;   // entry index within the track
-      if (SMOOTH)
-        live = smooth_step(b, g, t, k, r, lay, prev, valid, m, V, p, c, q, st, chi2, nval, bk, bk_stride);
-      else
-        live = fit_entry(a, g, static_cast<const T*>(nullptr), t, k, lay, prev, valid, m, V, p, c, q, st, chi2,
-                         nval, bk, bk_stride);
+      if constexpr (SMOOTH) {
+        const int64_t at = int64_t(r) * a.ld + t;
+        const StorePrediction<T> store{b.smooth_state + at, b.smooth_cov + at, a.ld * int64_t(a.max_len)};
+        live = fit_entry<true>(a, g, static_cast<const T*>(nullptr), t, k, lay, valid, m, V, f, bk, bk_stride, store);
+      } else {
+        live = fit_entry<true>(a, g, static_cast<const T*>(nullptr), t, k, lay, valid, m, V, f, bk, bk_stride);
+      }
       if (SMOOTH && !live) {
         // the pass stops here: the entries it will not reach get no
         // prediction (NaN), so that the combination skips them; a step that
         // failed in its update had stored its prediction already; a failed
         // first step or a bad layer id leaves the track unsmoothed
-        const int first = (k == 0 || (st & TRK_BAD_INPUT)) ? n_e - 2 : ((st & TRK_NONFINITE) ? r - 1 : r);
+        const int first = (k == 0 || (f.st & TRK_BAD_INPUT)) ? n_e - 2 : ((f.st & TRK_NONFINITE) ? r - 1 : r);
         for (int rr = first; rr >= k0; --rr) b.smooth_state[int64_t(rr) * a.ld + t] = k_nan<T>();
       }
     }
     wave_sync();   // every lane has read the chunk before the next one is staged
   }
   if (in_range) {
+    T p[6], c[21];
+    int q = f.s.q;
+    current_state(f, bk, bk_stride, p, c);
     if (run) reverse_direction(p, c, q);
-    store_fit(a, t, p, c, q, chi2, nval, st);
+    store_fit(a, t, p, c, q, f.chi2, f.nval, f.st);
   }
 }
 

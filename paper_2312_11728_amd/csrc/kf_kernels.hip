@@ -172,19 +172,17 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
     e0 = a.hit_offsets[t];
     len = int(a.hit_offsets[t + 1] - e0);
   }
-  uint32_t st = 0;
+  FitState<T> f;
+  f.st = 0;
+  if (in_range) begin_fit(a, t, g.bz, f, bk, bk_stride);
   if (len > a.max_len) {
-    st |= TRK_BAD_INPUT;
+    f.st |= TRK_BAD_INPUT;
     len = a.max_len;
   }
   sb.e0[lane] = e0;
   sb.len[lane] = len;
   const int kmax = wave_max(len);
-  T p[6], c[21];
-  int q = 0;
-  if (in_range) load_seed(a, t, g.bz, p, c, q, st);
-  T chi2 = T(0);
-  int nval = 0, prev = 0, k0 = -1;
+  int k0 = -1;
   bool live = in_range;
   const int64_t nh = a.n_hits;
   wave_sync();
@@ -226,20 +224,21 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
       if (k0 < 0) {
         if (!valid) continue;   // leading holes: the fit starts at the first valid entry
         k0 = k;
-        prev = lay;
       }
       T m[3], V[6];
 #pragma unroll
       for (int x = 0; x < 3; ++x) m[x] = sb.v[x][jj][lane];
 #pragma unroll
       for (int x = 0; x < 6; ++x) V[x] = sb.v[3 + x][jj][lane];
-      live = fit_entry(a, g, sal, t, k - k0, lay, prev, valid, m, V, p, c, q, st, chi2, nval, bk, bk_stride);
+      live = fit_entry<false>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride);
     }
     wave_sync();   // every lane has read the chunk before the next one is staged
   }
   if (in_range) {
-    if (k0 < 0) st |= TRK_BAD_INPUT;
-    store_fit(a, t, p, c, q, chi2, nval, st);
+    if (k0 < 0) f.st |= TRK_BAD_INPUT;
+    T p[6], c[21];
+    current_state(f, bk, bk_stride, p, c);
+    store_fit(a, t, p, c, f.s.q, f.chi2, f.nval, f.st);
   }
 }
 

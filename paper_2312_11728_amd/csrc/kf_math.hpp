@@ -470,8 +470,8 @@ struct PropTape {
 // The hook propagate() calls with the state on the surface just before the
 // layer's material is added (the default does nothing).
 struct NoPreMaterial {
-  template <typename T>
-  KF_HD void operator()(const T*, const T*) const {}
+  template <typename... S>
+  KF_HD void operator()(const S&...) const {}
 };
 
 template <typename T, typename PreMaterial = NoPreMaterial>

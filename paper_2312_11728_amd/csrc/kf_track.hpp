@@ -4,6 +4,7 @@
 
 #include "kf_kernels.hpp"
 #include "kf_math.hpp"
+#include "kf_surface.hpp"
 
 namespace kf {
 
@@ -151,76 +152,233 @@ struct PackedTrack {
   }
 };
 
+// alignment correction of a barrel hit (a rotation by a_rphi / R about the
+// beam axis and a shift a_z along it)
+template <typename T>
+KF_HD inline void align_hit(T m[3], const T* __restrict__ sal, int lay, T pos) {
+  T sa, ca;
+  k_sincos(sal[lay] * k_rcp(pos), &sa, &ca);
+  const T hx = m[0], hy = m[1];
+  m[0] = ca * hx - sa * hy;
+  m[1] = sa * hx + ca * hy;
+  m[2] += sal[kMaxLayers + lay];
+}
+
 // One entry of the forward fit: transport to layer `lay` (entry j > 0; the
 // first entry only adds its own layer's material), then, for a valid hit, the
 // alignment correction of the hit (barrel layers: rotation by a_rphi / R about
 // the beam axis and a shift a_z along it) and the update.  m is overwritten
 // with the aligned hit.  Returns false when the crossing fails; c2 is the
 // entry's chi2 contribution (0 for a hole).
-template <typename T>
+template <typename T, typename PreMaterial = NoPreMaterial>
 KF_HD inline bool step_forward(T p[6], T c[21], int& q, int j, int lay, int prev, bool valid, T m[3], const T V[6],
-                               const TrackGeom<T>& g, const T* __restrict__ sal, T& c2, uint32_t& sst) {
+                               const TrackGeom<T>& g, const T* __restrict__ sal, T& c2, uint32_t& sst,
+                               const PreMaterial& pre = PreMaterial()) {
   const int kind = g.kind[lay];
   if (j > 0) {
-    if (!propagate(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst)) return false;
+    if (!propagate(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst,
+                   static_cast<T*>(nullptr), static_cast<PropTape<T>*>(nullptr), pre))
+      return false;
   } else {
     add_material_here(p, c, kind, g.x0[lay], g.mass, sst);
   }
   c2 = T(0);
   if (valid) {
-    if (sal && kind == 0) {
-      const T ang = sal[lay] * k_rcp(g.pos[lay]);
-      T sa, ca;
-      k_sincos(ang, &sa, &ca);
-      const T hx = m[0], hy = m[1];
-      m[0] = ca * hx - sa * hy;
-      m[1] = sa * hx + ca * hy;
-      m[2] += sal[kMaxLayers + lay];
-    }
+    if (sal && kind == 0) align_hit(m, sal, lay, g.pos[lay]);
     update(p, c, q, m, V, c2, sst);
   }
   return true;
 }
 
-// The work of one entry of the forward fit, shared by every entry source:
-// layer check, checkpoint, backup of the state (bk: room for 28 values at
-// bk[k * bk_stride], kept out of registers -- in LDS on the device), the step,
-// and the roll-back to the backup when the step turns non-finite.  j: index
-// relative to the first valid entry.  Returns false when the track stops here
-// (the reason is in st).
+// The covariance a fit carries from entry to entry: the 6x6 one in FP32, the
+// 5x5 one of the surface frame in FP64.  In FP64 the surface frame saves a
+// third of the step.  In FP32 the 6x6 step keeps its rounding: while 1/pT is
+// compatible with zero its rounding decides the charge that a filtered state
+// is kept with, which the smoother and the final fit's decisions depend on,
+// so that another rounding (the 5x5 form's errors are no larger) changes one
+// smoothed entry in a million visibly.
 template <typename T>
-KF_HD inline bool fit_entry(const FitArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t, int j,
-                            int lay, int& prev, bool valid, T m[3], const T V[6], T p[6], T c[21], int& q,
-                            uint32_t& st, T& chi2, int& nval, T* bk, int bk_stride) {
-  if (lay < 0 || lay >= g.n_layers) {
-    st |= TRK_BAD_INPUT;
-    return false;
-  }
-  if (a.ckpt && j >= 1 && ((j - 1) % a.seg) == 0) write_checkpoint(a, t, (j - 1) / a.seg, p, c, q);
+constexpr bool kOnSurface = sizeof(T) == 8;
+
+// A track on its way through the forward or backward fit.  bk: room for 28
+// values at bk[k * bk_stride], kept out of registers (in LDS on the device).
+// FP32: s.p, s.q and c6 hold the state, bk the backup of a step.  FP64:
+// done = 0: no entry completed, bk holds the starting state and its 6x6
+// covariance.  done = 1: the first entry completed, bk holds its result (a
+// 6x6 covariance of full rank, which a checkpoint or the output may need) and
+// s the covariance confined to the track's plane.  done = 2: s is
+// on the last completed entry's surface; bk is the backup of a step.
+template <typename T>
+struct FitState {
+  SurfState<T> s;
+  T c6[kOnSurface<T> ? 1 : 21];
+  int done, prev, nval;
+  uint32_t st;
+  T chi2;
+};
+
+template <typename T>
+KF_HD inline void save_full(T* bk, int bk_stride, const T p[6], const T c[21]) {
 #pragma unroll
   for (int i = 0; i < 6; ++i) bk[i * bk_stride] = p[i];
 #pragma unroll
   for (int i = 0; i < 21; ++i) bk[(6 + i) * bk_stride] = c[i];
-  const int qq = q;
+}
+
+template <typename T>
+KF_HD inline void load_full(const T* bk, int bk_stride, T p[6], T c[21]) {
+#pragma unroll
+  for (int i = 0; i < 6; ++i) p[i] = bk[i * bk_stride];
+#pragma unroll
+  for (int i = 0; i < 21; ++i) c[i] = bk[(6 + i) * bk_stride];
+}
+
+// the track's state and 6x6 covariance after its last completed entry
+template <typename T>
+KF_HD inline void current_state(const FitState<T>& f, const T* bk, int bk_stride, T p[6], T c[21]) {
+  if (kOnSurface<T> && f.done < 2) {
+    load_full(bk, bk_stride, p, c);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 6; ++i) p[i] = f.s.p[i];
+  if constexpr (kOnSurface<T>) {
+    expand_cov(f.s, c);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 21; ++i) c[i] = f.c6[i];
+  }
+}
+
+// the starting state of a fit
+template <typename T>
+KF_HD inline void start_state(FitState<T>& f, T* bk, int bk_stride, const T p[6], const T c[21], int q) {
+  f.s.q = q;
+  f.done = 0;
+  f.prev = 0;
+  f.nval = 0;
+  f.chi2 = T(0);
+  if constexpr (kOnSurface<T>) {
+    save_full(bk, bk_stride, p, c);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) f.s.p[i] = p[i];
+#pragma unroll
+    for (int i = 0; i < 21; ++i) f.c6[i] = c[i];
+  }
+}
+
+// One entry of the forward (BACK false) or backward fit: layer check,
+// checkpoint (forward), the step to the entry's layer with its material and,
+// for a valid hit, the update; rolled back when it turns non-finite.  j:
+// index relative to the track's first entry (forward: its first valid one),
+// which takes its layer's material where the track is.  pre is called with
+// the state on a later entry's surface before the layer's material.  Returns
+// false when the track stops here (the reason is in f.st).
+//
+// Surface frame: the first entry works on the starting state's 6x6 covariance
+// and leaves it confined to the track's plane.  The 6x6 update has one place,
+// for the first entry and for the lanes that update5 turns away: most waves
+// pass it by.
+template <bool BACK, typename T, typename PreMaterial = NoPreMaterial>
+KF_HD inline bool fit_entry(const FitArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t, int j,
+                            int lay, bool valid, T m[3], const T V[6], FitState<T>& f, T* bk, int bk_stride,
+                            const PreMaterial& pre = PreMaterial()) {
+  if (lay < 0 || lay >= g.n_layers) {
+    f.st |= TRK_BAD_INPUT;
+    return false;
+  }
+  if constexpr (!kOnSurface<T>) {
+    T* p = f.s.p;
+    T* c = f.c6;
+    if (!BACK && a.ckpt && j >= 1 && ((j - 1) % a.seg) == 0) write_checkpoint(a, t, (j - 1) / a.seg, p, c, f.s.q);
+    save_full(bk, bk_stride, p, c);
+    const int q = f.s.q;
+    uint32_t sst = 0;
+    T c2;
+    if (!step_forward(p, c, f.s.q, j, lay, f.prev, valid, m, V, g, sal, c2, sst, pre)) {
+      f.st |= sst;
+      return false;
+    }
+    f.st |= sst;
+    if (!all_finite(p, c, c2)) {
+      f.st |= TRK_NONFINITE;
+      load_full(bk, bk_stride, p, c);
+      f.s.q = q;
+      return false;
+    }
+    f.chi2 += c2;
+    f.nval += valid ? 1 : 0;
+    f.prev = lay;
+    return true;
+  }
+  SurfState<T>& s = f.s;
+  const int q = s.q, kind = g.kind[lay];
+  const T x0 = g.x0[lay];
   uint32_t sst = 0;
-  T c2;
-  if (!step_forward(p, c, q, j, lay, prev, valid, m, V, g, sal, c2, sst)) {
-    st |= sst;
+  T c2 = T(0), C[21];
+  bool six = j == 0;   // C holds the covariance
+  if (six) {
+    load_full(bk, bk_stride, s.p, C);
+    add_material_here(s.p, C, kind, x0, g.mass, sst);
+  } else {
+    if (!BACK && a.ckpt && ((j - 1) % a.seg) == 0) {
+      T p[6];
+      current_state(f, bk, bk_stride, p, C);
+      write_checkpoint(a, t, (j - 1) / a.seg, p, C, q);
+    }
+    if (f.done == 2) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) bk[i * bk_stride] = s.p[i];
+#pragma unroll
+      for (int i = 0; i < 15; ++i) bk[(6 + i) * bk_stride] = s.c[i];
+      bk[21 * bk_stride] = s.tx;
+      bk[22 * bk_stride] = s.ty;
+    }
+    if (!propagate5(s, kind, g.pos[lay], x0, lay == f.prev, g.bz, g.mass, sst, pre)) {
+      f.st |= sst;
+      return false;
+    }
+  }
+  if (valid) {
+    if (sal && kind == 0) align_hit(m, sal, lay, g.pos[lay]);
+    if (j > 0 && !update5(s, m, V, c2, sst)) {
+      six = true;
+      expand_cov(s, C);
+    }
+  }
+  bool ok;
+  if (six) {
+    if (valid) update(s.p, C, s.q, m, V, c2, sst);
+    ok = all_finite(s.p, C, c2);
+    if (ok && j == 0) {
+      save_full(bk, bk_stride, s.p, C);
+      confine_to_track_plane(C, g.bz, s);
+    } else {
+      compress_cov(C, s);
+    }
+  } else {
+    ok = all_finite5(s, c2);
+  }
+  f.st |= sst;
+  if (!ok) {
+    f.st |= TRK_NONFINITE;
+    s.q = q;
+    if (f.done == 2) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) s.p[i] = bk[i * bk_stride];
+#pragma unroll
+      for (int i = 0; i < 15; ++i) s.c[i] = bk[(6 + i) * bk_stride];
+      s.tx = bk[21 * bk_stride];
+      s.ty = bk[22 * bk_stride];
+      s.kind = g.kind[f.prev];
+    }
     return false;
   }
-  if (!all_finite(p, c, c2)) {
-    st |= sst | TRK_NONFINITE;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) p[i] = bk[i * bk_stride];
-#pragma unroll
-    for (int i = 0; i < 21; ++i) c[i] = bk[(6 + i) * bk_stride];
-    q = qq;
-    return false;
-  }
-  st |= sst;
-  chi2 += c2;
-  nval += valid ? 1 : 0;
-  prev = lay;
+  f.done = j == 0 ? 1 : 2;
+  f.chi2 += c2;
+  f.nval += valid ? 1 : 0;
+  f.prev = lay;
   return true;
 }
 
@@ -254,6 +412,15 @@ KF_HD inline void load_seed(const FitArgs<T>& a, int64_t t, T bz, T p[6], T c[21
 }
 
 template <typename T>
+KF_HD inline void begin_fit(const FitArgs<T>& a, int64_t t, T bz, FitState<T>& f, T* bk, int bk_stride) {
+  T p[6], c[21];
+  f.st = 0;
+  int q;
+  load_seed(a, t, bz, p, c, q, f.st);
+  start_state(f, bk, bk_stride, p, c, q);
+}
+
+template <typename T>
 KF_HD inline void store_fit(const FitArgs<T>& a, int64_t t, const T p[6], const T c[21], int q, T chi2, int nval,
                             uint32_t st) {
 #pragma unroll
@@ -272,20 +439,16 @@ KF_HD inline void store_fit(const FitArgs<T>& a, int64_t t, const T p[6], const 
 template <typename T, typename Acc>
 KF_HD inline void fit_track(const FitArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
                             const Acc& acc, int len, T* bk, int bk_stride) {
-  T p[6], c[21];
-  int q;
-  uint32_t st = 0;
-  load_seed(a, t, g.bz, p, c, q, st);
+  FitState<T> f;
+  begin_fit(a, t, g.bz, f, bk, bk_stride);
   if (len > a.max_len) {
-    st |= TRK_BAD_INPUT;
+    f.st |= TRK_BAD_INPUT;
     len = a.max_len;
   }
   int k0 = 0;
   while (k0 < len && !acc.valid(k0)) ++k0;
-  T chi2 = T(0);
-  int nval = 0;
   if (k0 >= len) {
-    st |= TRK_BAD_INPUT;
+    f.st |= TRK_BAD_INPUT;
   } else {
     // entry data are loaded one entry ahead so that the loads of entry k+1
     // overlap the arithmetic of entry k
@@ -293,7 +456,6 @@ KF_HD inline void fit_track(const FitArgs<T>& a, const TrackGeom<T>& g, const T*
     bool valid_n;
     T m_n[3], V_n[6];
     acc.load(k0, lay_n, valid_n, m_n, V_n);
-    int prev = lay_n;
     for (int k = k0; k < len; ++k) {
       const int lay = lay_n;
       const bool valid = valid_n;
@@ -303,10 +465,12 @@ KF_HD inline void fit_track(const FitArgs<T>& a, const TrackGeom<T>& g, const T*
 #pragma unroll
       for (int i = 0; i < 6; ++i) V[i] = V_n[i];
       if (k + 1 < len) acc.load(k + 1, lay_n, valid_n, m_n, V_n);
-      if (!fit_entry(a, g, sal, t, k - k0, lay, prev, valid, m, V, p, c, q, st, chi2, nval, bk, bk_stride)) break;
+      if (!fit_entry<false>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride)) break;
     }
   }
-  store_fit(a, t, p, c, q, chi2, nval, st);
+  T p[6], c[21];
+  current_state(f, bk, bk_stride, p, c);
+  store_fit(a, t, p, c, f.s.q, f.chi2, f.nval, f.st);
 }
 
 // Fit of the track in slot / index `i`: LAYOUT 2 reads the packed layout,
