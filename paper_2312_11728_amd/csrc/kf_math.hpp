@@ -97,6 +97,16 @@ KF_HD inline float k_rcp(float x) {
 }
 KF_HD inline double k_rcp(double x) { return 1.0 / x; }
 
+// true when the condition holds for every active lane of the wave (on the
+// host: for the one track)
+KF_HD inline bool all_lanes(bool v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_ballot_w64(!v) == 0;
+#else
+  return v;
+#endif
+}
+
 template <typename T>
 KF_HD inline T wrap_phi(T phi) {
   // to (-pi, pi]
@@ -115,32 +125,6 @@ KF_HD inline void reverse_direction(T p[6], T c[21], int& q) {
   q = -q;
 #pragma unroll
   for (int j = 0; j < 5; ++j) c[sym(5, j)] = -c[sym(5, j)];
-}
-
-// The covariance of a state on a surface has the surface normal as a null
-// vector: C <- (I - n n^T) C (I - n n^T) on the position block, n = (x, y) / R
-// for a barrel of radius R, the z row and column cleared for a disk (the same
-// projection propagate() applies after a crossing).  A covariance that already
-// has the null vector is unchanged up to rounding; a stored and scaled-up one
-// loses its rounding residue along n.
-template <typename T>
-KF_HD inline void impose_surface(T c[21], const T p[6], int kind, T pos) {
-  if (kind == 1) {
-#pragma unroll
-    for (int j = 0; j < 6; ++j) c[sym(2, j)] = T(0);
-    return;
-  }
-  const T rinv = k_rcp(pos);
-  const T nx = p[0] * rinv, ny = p[1] * rinv;
-  T cn[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) cn[i] = c[sym(i, 0)] * nx + c[sym(i, 1)] * ny;
-  const T nn = cn[0] * nx + cn[1] * ny;
-  const T nv[6] = {nx, ny, T(0), T(0), T(0), T(0)};
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j <= i; ++j) c[sym(i, j)] += -cn[i] * nv[j] - nv[i] * cn[j] + nn * nv[i] * nv[j];
 }
 
 // sin(h)/h
@@ -208,6 +192,21 @@ KF_HD inline T path_from_sigma(T num, T den, T w) {
     return T(2) * sig * atanc(w * sig);
   }
   return T(2) * k_atan2(t, den) * k_rcp(w);
+}
+
+KF_HD inline float k_fma(float a, float b, float c) { return fmaf(a, b, c); }
+KF_HD inline double k_fma(double a, double b, double c) { return fma(a, b, c); }
+
+// x^2 + y^2 with the square of x (kFuseX) or of y (kFuseY) in the fused
+// multiply-add.  Left to the compiler (kFuseAny), the choice changes with the
+// code around it, and with it the last bit of a track's radius; the FP32 fits
+// fix it, so that each family of hit layouts keeps its results.
+constexpr int kFuseAny = 0, kFuseX = 1, kFuseY = 2;
+template <int R2, typename T>
+KF_HD inline T radius2(T x, T y) {
+  if constexpr (R2 == kFuseX) return k_fma(x, x, y * y);
+  if constexpr (R2 == kFuseY) return k_fma(y, y, x * x);
+  return x * x + y * y;
 }
 
 // Point of the helix at transverse path s, from the trigonometry of the start
@@ -287,12 +286,60 @@ KF_HD inline void helix_nudge(HelixPt<T>& o, T w, T cot, T ds) {
   o.shc += dh * dshc;
 }
 
+// The first admissible root of the barrel crossing: sig1 = qq / alpha and
+// sig2 = -D / (2 qq), each mapped onto the turn (lo, lo + 2 pi/|w|].
+template <typename T>
+KF_HD inline bool first_root(T qq, T alpha, T D, T w, T lo, T& best) {
+  bool found = false;
+  if (qq != T(0) || alpha != T(0)) {
+    T s1 = path_from_sigma(qq, alpha, w);
+    if (k_finite(s1)) {
+      s1 = to_window(s1, lo, w);
+      if (s1 > lo) {
+        best = s1;
+        found = true;
+      }
+    }
+  }
+  if (qq != T(0)) {
+    T s2 = path_from_sigma(T(-0.5) * D, qq, w);
+    if (k_finite(s2)) {
+      s2 = to_window(s2, lo, w);
+      if (s2 > lo && (!found || s2 < best)) {
+        best = s2;
+        found = true;
+      }
+    }
+  }
+  return found;
+}
+
+// sig2 alone, where it is known to come first: alpha > 0 and either qq > 0,
+// D < 0 and sig1 >= 1.5 sig2 (both roots ahead, sig2 the nearer by more than
+// rounding) or qq <= -alpha (sig1 <= -1: that root lies more than 1 cm behind
+// and belongs to the far end of the turn, at least pi / |w| away), with
+// |w s2| <= 1, |w| <= 1.5 and lo < s2.  Between barrel layers, outwards or
+// inwards, that is every track, and a wave of such tracks skips the other
+// root's angle and the mapping of both onto the turn.  The value is
+// first_root()'s: to_window() returns lo + (s - lo) for a path inside the
+// turn.
+template <typename T>
+KF_HD inline bool near_root(T qq, T alpha, T D, T w, T lo, T& best) {
+  const T s2 = path_from_sigma(T(-0.5) * D, qq, w);
+  const T aw = k_abs(w), d2 = s2 - lo;
+  const bool ahead = qq > T(0) ? D < T(0) && qq * qq >= T(0.75) * alpha * -D : -qq >= alpha;
+  if (!(ahead && alpha > T(0) && aw > T(0) && aw <= T(1.5) && k_abs(w * s2) <= T(1) && d2 > T(0) && d2 * aw <= T(3)))
+    return false;
+  best = lo + d2;
+  return best > lo;
+}
+
 // First admissible crossing of the layer surface.  Barrel: roots of
 // r(s)^2 = R^2 written as alpha sig^2 + 2 A sig - D/2 = 0 with tan(u/2) = w sig,
 // A = x cos phi + y sin phi, B = x sin phi - y cos phi, D = R^2 - r^2,
 // alpha = 2 (1 - w B) - w^2 D / 2; then one Newton step on r^2 - R^2.
 // Disk: s = (Z - z)/cot(theta).  On success fills the helix point at s.
-template <typename T>
+template <int R2, typename T>
 KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, bool same, T& s_out,
                     HelixPt<T>& hp) {
   T lo = same ? T(kSSame) : T(-kSBack);
@@ -308,7 +355,7 @@ KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, b
   T x = p[0], y = p[1];
   T A = x * cphi + y * sphi;
   T B = x * sphi - y * cphi;
-  T r0 = k_sqrt(x * x + y * y);
+  T r0 = k_sqrt(radius2<R2>(x, y));
   T D = (pos - r0) * (pos + r0);
   T alpha = T(2) * (T(1) - w * B) - T(0.5) * w * w * D;
   T disc = A * A + T(0.5) * alpha * D;
@@ -316,30 +363,7 @@ KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, b
   T sq = k_sqrt(disc);
   T qq = -(A + k_copysign(sq, A));
   T best = T(0);
-  bool found = false;
-  // root 1: sig = qq / alpha
-  if (qq != T(0) || alpha != T(0)) {
-    T s1 = path_from_sigma(qq, alpha, w);
-    if (k_finite(s1)) {
-      s1 = to_window(s1, lo, w);
-      if (s1 > lo) {
-        best = s1;
-        found = true;
-      }
-    }
-  }
-  // root 2: sig = -D / (2 qq)
-  if (qq != T(0)) {
-    T s2 = path_from_sigma(T(-0.5) * D, qq, w);
-    if (k_finite(s2)) {
-      s2 = to_window(s2, lo, w);
-      if (s2 > lo && (!found || s2 < best)) {
-        best = s2;
-        found = true;
-      }
-    }
-  }
-  if (!found) return false;
+  if (!near_root(qq, alpha, D, w, lo, best) && !first_root(qq, alpha, D, w, lo, best)) return false;
   // Newton polish on h(s) = r(s)^2 - R^2: two steps (the second matters near
   // tangency, where h'(s) is small and the closed-form root is least
   // accurate).  In FP32 a correction whose second-order terms stay below a
@@ -400,8 +424,10 @@ KF_HD inline void add_q(T c[21], T ipt, T sth, T cot, T var) {
 // helix partials at fixed path (identity but for G03, G04, G13, G14, G25,
 // G43), g = d(state)/ds = (g0, g1, g2, 0, g4, 0) and d = ds/dp.  Expanded as
 // G C G^T + g v^T + v g^T + a g g^T with v = G C d and a = d^T C d, which
-// uses the sparsity of G and never forms F.
-template <typename T>
+// uses the sparsity of G and never forms F.  BARREL: d[2] = d[5] = 0 (the
+// crossing of a cylinder about z).  The products with elements that are zero
+// are left out everywhere; adding them changes no bit of a finite result.
+template <bool BARREL, typename T>
 KF_HD inline void transport_cov(T c[21], const T d[6], T G03, T G04, T G13, T G14, T G25, T G43, T g0, T g1, T g2,
                                 T g4) {
   // wv = C d, a = d^T C d, v = G wv
@@ -410,12 +436,14 @@ KF_HD inline void transport_cov(T c[21], const T d[6], T G03, T G04, T G13, T G1
   for (int i = 0; i < 6; ++i) {
     T acc = T(0);
 #pragma unroll
-    for (int j = 0; j < 6; ++j) acc += c[sym(i, j)] * d[j];
+    for (int j = 0; j < 6; ++j)
+      if (!BARREL || (j != 2 && j != 5)) acc += c[sym(i, j)] * d[j];
     wv[i] = acc;
   }
   T a = T(0);
 #pragma unroll
-  for (int i = 0; i < 6; ++i) a += d[i] * wv[i];
+  for (int i = 0; i < 6; ++i)
+    if (!BARREL || (i != 2 && i != 5)) a += d[i] * wv[i];
   T v[6];
   v[0] = wv[0] + G03 * wv[3] + G04 * wv[4];
   v[1] = wv[1] + G13 * wv[3] + G14 * wv[4];
@@ -450,9 +478,58 @@ KF_HD inline void transport_cov(T c[21], const T d[6], T G03, T G04, T G13, T G1
   for (int i = 0; i < 6; ++i) {
 #pragma unroll
     for (int j = 0; j <= i; ++j) {
-      c[sym(i, j)] = N[sym(i, j)] + gg[i] * v[j] + v[i] * gg[j] + a * gg[i] * gg[j];
+      const bool gi = i != 3 && i != 5, gj = j != 3 && j != 5;   // gg[i], gg[j] not zero
+      T x = N[sym(i, j)];
+      if (gi) x = x + gg[i] * v[j];
+      if (gj) x = x + v[i] * gg[j];
+      if (gi && gj) x = x + a * gg[i] * gg[j];
+      c[sym(i, j)] = x;
     }
   }
+}
+
+// C <- (I - n n^T) C (I - n n^T) on the position block for n = (nx, ny, 0).
+// The products with the zeros of n are left out; the sums that remain are not
+// fused, as the whole expression would not be.
+template <typename T>
+KF_HD inline void project_out_radial(T c[21], T nx, T ny) {
+  T cn[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) cn[i] = c[sym(i, 0)] * nx + c[sym(i, 1)] * ny;
+  const T nn = cn[0] * nx + cn[1] * ny;
+  const T nv[2] = {nx, ny};
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+#pragma unroll
+    for (int j = 0; j <= i && j < 2; ++j) {
+      T x;
+      if (i < 2) {
+        x = -cn[i] * nv[j] - nv[i] * cn[j] + nn * nv[i] * nv[j];
+      } else {
+        x = -cn[i] * nv[j];
+      }
+      {
+#pragma clang fp contract(off)
+        c[sym(i, j)] = c[sym(i, j)] + x;
+      }
+    }
+}
+
+// The covariance of a state on a surface has the surface normal as a null
+// vector: C <- (I - n n^T) C (I - n n^T) on the position block, n = (x, y) / R
+// for a barrel of radius R, the z row and column cleared for a disk (the same
+// projection propagate() applies after a crossing).  A covariance that already
+// has the null vector is unchanged up to rounding; a stored and scaled-up one
+// loses its rounding residue along n.
+template <typename T>
+KF_HD inline void impose_surface(T c[21], const T p[6], int kind, T pos) {
+  if (kind == 1) {
+#pragma unroll
+    for (int j = 0; j < 6; ++j) c[sym(2, j)] = T(0);
+    return;
+  }
+  const T rinv = k_rcp(pos);
+  project_out_radial(c, p[0] * rinv, p[1] * rinv);
 }
 
 // Intermediates of one propagation, recorded for the reverse pass.
@@ -474,7 +551,7 @@ struct NoPreMaterial {
   KF_HD void operator()(const S&...) const {}
 };
 
-template <typename T, typename PreMaterial = NoPreMaterial>
+template <int R2 = kFuseAny, typename T, typename PreMaterial = NoPreMaterial>
 KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool same, bool material, T bz,
                      T mass, uint32_t& st, T* path = nullptr, PropTape<T>* tape = nullptr,
                      const PreMaterial& pre = PreMaterial()) {
@@ -487,7 +564,7 @@ KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool 
   const T cot = cth * isth;
   T s;
   HelixPt<T> hp;
-  if (!crossing(p, sphi, cphi, cot, w, kind, pos, same, s, hp)) {
+  if (!crossing<R2>(p, sphi, cphi, cot, w, kind, pos, same, s, hp)) {
     st |= TRK_NO_CROSSING;
     return false;
   }
@@ -548,7 +625,11 @@ KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool 
     tape->inv = (kind == 0) ? -k_rcp(x * cphm + y * sphm) : -k_rcp(cot);
     tape->hp = hp;
   }
-  transport_cov(c, d, G03, G04, G13, G14, G25, G43, cphm, sphm, cot, w);
+  // one form for the whole wave: a wave with both kinds would run both
+  if (all_lanes(kind == 0))
+    transport_cov<true>(c, d, G03, G04, G13, G14, G25, G43, cphm, sphm, cot, w);
+  else
+    transport_cov<false>(c, d, G03, G04, G13, G14, G25, G43, cphm, sphm, cot, w);
   // The exact C' has the surface normal n (in position) as a null vector: a
   // state confined to the surface cannot move along n.  Rounding in the
   // cancellation F = G + g d^T leaves a residue of order eps * (G C G^T) there,
@@ -559,16 +640,7 @@ KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool 
 #pragma unroll
     for (int j = 0; j < 6; ++j) c[sym(2, j)] = T(0);
   } else {
-    const T nx = x * rinv, ny = y * rinv;
-    T cn[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) cn[i] = c[sym(i, 0)] * nx + c[sym(i, 1)] * ny;
-    const T nn = cn[0] * nx + cn[1] * ny;
-    const T nv[6] = {nx, ny, T(0), T(0), T(0), T(0)};
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int j = 0; j <= i; ++j) c[sym(i, j)] += -cn[i] * nv[j] - nv[i] * cn[j] + nn * nv[i] * nv[j];
+    project_out_radial(c, x * rinv, y * rinv);
   }
   p[0] = x;
   p[1] = y;
@@ -585,7 +657,7 @@ KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool 
 }
 
 // Material of a layer added at the current state (the seed's own layer).
-template <typename T>
+template <int R2 = kFuseAny, typename T>
 KF_HD void add_material_here(const T p[6], T c[21], int kind, T x_over_x0, T mass, uint32_t& st) {
   T sth, cth;
   k_sincos(p[5], &sth, &cth);
@@ -593,7 +665,7 @@ KF_HD void add_material_here(const T p[6], T c[21], int kind, T x_over_x0, T mas
   if (kind == 0) {
     T sph, cph;
     k_sincos(p[4], &sph, &cph);
-    const T r = k_sqrt(p[0] * p[0] + p[1] * p[1]);
+    const T r = k_sqrt(radius2<R2>(p[0], p[1]));
     ca = k_abs(sth * (cph * p[0] + sph * p[1]) * k_rcp(r));
   } else {
     ca = k_abs(cth);
@@ -850,8 +922,22 @@ KF_HD void update(T p[6], T c[21], int& q, const T m[3], const T V[6], T& chi2, 
   update_core<T>(p, c, q, m, V, chi2, st);
 }
 
+// The largest magnitude with NaN above everything: finite iff all are (one
+// three-operand maximum for every two values, where a class test of each
+// takes two instructions).
+KF_HD inline float max_abs(float m, float x) { return __builtin_elementwise_maximum(m, k_abs(x)); }
+KF_HD inline double max_abs(double m, double x) { return __builtin_elementwise_maximum(m, k_abs(x)); }
+
 template <typename T>
 KF_HD inline bool all_finite(const T p[6], const T c[21], T chi2) {
+  if constexpr (sizeof(T) == 4) {
+    T m = k_abs(chi2);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) m = max_abs(m, p[i]);
+#pragma unroll
+    for (int i = 0; i < 21; ++i) m = max_abs(m, c[i]);
+    return k_finite(m);
+  }
   bool ok = k_finite(chi2);
 #pragma unroll
   for (int i = 0; i < 6; ++i) ok = ok && k_finite(p[i]);

@@ -154,7 +154,7 @@ KF_HD bool propagate_plane(T p[6], T c[21], int q, const Plane<T>& pl, bool mate
   d[3] = (pl.nx * G03 + pl.ny * G13) * inv;
   d[4] = (pl.nx * G04 + pl.ny * G14) * inv;
   d[5] = pl.nz * G25 * inv;
-  transport_cov(c, d, G03, G04, G13, G14, G25, G43, cphm, sphm, cot, w);
+  transport_cov<false>(c, d, G03, G04, G13, G14, G25, G43, cphm, sphm, cot, w);
   project_out_normal(c, pl.nx, pl.ny, pl.nz);
   p[0] = hp.x;
   p[1] = hp.y;

@@ -284,8 +284,6 @@ KF_HD inline bool cross_surface(const T p[6], T sphi, T cphi, T cot, T w, int ki
   return true;
 }
 
-KF_HD inline double s_fma(double a, double b, double c) { return fma(a, b, c); }
-
 // sum_j r[j] x[j] + x0 over the elements that a row between barrel layers has
 // (BARREL: not the columns b and theta) or over all five, term by term with
 // fused multiply-adds: a zero element adds exactly nothing, so both forms
@@ -293,10 +291,10 @@ KF_HD inline double s_fma(double a, double b, double c) { return fma(a, b, c); }
 template <bool BARREL, typename T>
 KF_HD inline T row_dot(const T r[5], T c0, T c1, T c2, T c3, T c4) {
   T v = r[0] * c0;
-  if (!BARREL) v = s_fma(r[1], c1, v);
-  v = s_fma(r[2], c2, v);
-  v = s_fma(r[3], c3, v);
-  if (!BARREL) v = s_fma(r[4], c4, v);
+  if (!BARREL) v = k_fma(r[1], c1, v);
+  v = k_fma(r[2], c2, v);
+  v = k_fma(r[3], c3, v);
+  if (!BARREL) v = k_fma(r[4], c4, v);
   return v;
 }
 
@@ -311,16 +309,16 @@ KF_HD inline void transport5(T c[15], const T ja[5], const T jb[5], const T jp[5
     const T c0 = c[sym(SA, j)], c1 = c[sym(SB, j)], c2 = c[sym(SI, j)], c3 = c[sym(SP, j)], c4 = c[sym(ST, j)];
     Ma[j] = row_dot<BARREL>(ja, c0, c1, c2, c3, c4);
     Mp[j] = row_dot<BARREL>(jp, c0, c1, c2, c3, c4);
-    Mb[j] = s_fma(jb[4], c4, row_dot<true>(jb, c0, c1, c2, c3, c4));
-    Mb[j] = BARREL ? Mb[j] + c1 : s_fma(jb[1], c1, Mb[j]);
+    Mb[j] = k_fma(jb[4], c4, row_dot<true>(jb, c0, c1, c2, c3, c4));
+    Mb[j] = BARREL ? Mb[j] + c1 : k_fma(jb[1], c1, Mb[j]);
   }
   c[sym(SA, SA)] = row_dot<BARREL>(ja, Ma[0], Ma[1], Ma[2], Ma[3], Ma[4]);
   c[sym(SB, SA)] = row_dot<BARREL>(ja, Mb[0], Mb[1], Mb[2], Mb[3], Mb[4]);
   c[sym(SP, SA)] = row_dot<BARREL>(ja, Mp[0], Mp[1], Mp[2], Mp[3], Mp[4]);
   c[sym(SP, SP)] = row_dot<BARREL>(jp, Mp[0], Mp[1], Mp[2], Mp[3], Mp[4]);
   c[sym(SP, SB)] = row_dot<BARREL>(jp, Mb[0], Mb[1], Mb[2], Mb[3], Mb[4]);
-  T bb = s_fma(jb[4], Mb[4], row_dot<true>(jb, Mb[0], Mb[1], Mb[2], Mb[3], Mb[4]));
-  bb = BARREL ? bb + Mb[1] : s_fma(jb[1], Mb[1], bb);
+  T bb = k_fma(jb[4], Mb[4], row_dot<true>(jb, Mb[0], Mb[1], Mb[2], Mb[3], Mb[4]));
+  bb = BARREL ? bb + Mb[1] : k_fma(jb[1], Mb[1], bb);
   c[sym(SB, SB)] = bb;
   c[sym(SI, SA)] = Ma[SI];
   c[sym(SI, SB)] = Mb[SI];
@@ -328,16 +326,6 @@ KF_HD inline void transport5(T c[15], const T ja[5], const T jb[5], const T jp[5
   c[sym(ST, SA)] = Ma[ST];
   c[sym(ST, SB)] = Mb[ST];
   c[sym(ST, SP)] = Mp[ST];
-}
-
-// true when the condition holds for every active lane of the wave (on the
-// host: for the one track)
-KF_HD inline bool all_lanes(bool v) {
-#ifdef __HIP_DEVICE_COMPILE__
-  return __builtin_amdgcn_ballot_w64(!v) == 0;
-#else
-  return v;
-#endif
 }
 
 // Highland angle squared (highland_var, without its square roots: theta0^2 is
