@@ -48,36 +48,17 @@ __device__ void refill_wave_staged(const AdjArgs<T>& a, const TrackGeom<T>& g, c
     len = int(f.hit_offsets[t + 1] - e0);
     if (len > f.max_len) len = f.max_len;
   }
-  sb.e0[lane] = e0;
+  sb.e0[lane] = int32_t(e0);
   sb.len[lane] = len;
   const int kmax = wave_max(len);
-  const int64_t nh = f.n_hits, n = f.n, cst = f.ld * int64_t(f.n_seg);
+  const int64_t n = f.n, cst = f.ld * int64_t(f.n_seg);
   T p[6], c[21];
   int q = 0, prev = 0, prev_lay = 0, k0 = -1;
   wave_sync();
+  StageRows<J> rows;
+  stage_rows(sb, rows);
   for (int j0 = 0; j0 < kmax; j0 += J) {
-    int32_t lvr[J];
-    T vr[J][9];
-#pragma unroll
-    for (int r = 0; r < J; ++r) {
-      const int idx = r * 64 + lane;
-      const int l = idx / J, jj = idx % J;
-      const int ln = sb.len[l];
-      const int64_t e = ln > 0 ? sb.e0[l] + min(j0 + jj, ln - 1) : 0;
-      lvr[r] = int32_t(uint16_t(f.hit_layer[e])) | (f.hit_valid[e] ? (1 << 16) : 0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) vr[r][k] = f.hit_pos[k * nh + e];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) vr[r][3 + k] = f.hit_cov[k * nh + e];
-    }
-#pragma unroll
-    for (int r = 0; r < J; ++r) {
-      const int idx = r * 64 + lane;
-      const int l = idx / J, jj = idx % J;
-      sb.lv[jj][l] = lvr[r];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) sb.v[k][jj][l] = vr[r][k];
-    }
+    stage_chunk<1>(f, rows, j0, sb);
     wave_sync();
     const int jn = min(J, kmax - j0);
     for (int jj = 0; jj < jn; ++jj) {

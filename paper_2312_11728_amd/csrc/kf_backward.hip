@@ -301,39 +301,15 @@ __device__ void backward_wave_staged(const BwdArgs<T>& b, const TrackGeom<T>& g,
     }
     start_state(f, bk, bk_stride, p, c, q);
   }
-  sb.e0[lane] = last;
+  sb.e0[lane] = int32_t(last);
   sb.len[lane] = len;
   const int kmax = wave_max(len);
   bool live = run;
-  const int64_t nh = a.n_hits;
   wave_sync();
+  StageRows<J> rows;
+  stage_rows(sb, rows);
   for (int j0 = 0; j0 < kmax; j0 += J) {
-    // all J rows are loaded before any is written to LDS (one memory round
-    // trip per chunk); a slot past the end of its pass loads the pass's last
-    // entry (the track's first valid one) and is never read; kmax > 0 means
-    // some track has an entry, so entry 0 exists for the slots of no track
-    int32_t lvr[J];
-    T vr[J][9];
-#pragma unroll
-    for (int r = 0; r < J; ++r) {
-      const int idx = r * 64 + lane;
-      const int l = idx / J, jj = idx % J;
-      const int ln = sb.len[l];
-      const int64_t e = ln > 0 ? sb.e0[l] - min(j0 + jj, ln - 1) : 0;
-      lvr[r] = int32_t(uint16_t(a.hit_layer[e])) | (a.hit_valid[e] ? (1 << 16) : 0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) vr[r][k] = a.hit_pos[k * nh + e];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) vr[r][3 + k] = a.hit_cov[k * nh + e];
-    }
-#pragma unroll
-    for (int r = 0; r < J; ++r) {
-      const int idx = r * 64 + lane;
-      const int l = idx / J, jj = idx % J;
-      sb.lv[jj][l] = lvr[r];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) sb.v[k][jj][l] = vr[r][k];
-    }
+    stage_chunk<-1>(a, rows, j0, sb);
     wave_sync();
     const int jn = min(J, kmax - j0);
     for (int jj = 0; jj < jn; ++jj) {
@@ -351,9 +327,9 @@ __device__ void backward_wave_staged(const BwdArgs<T>& b, const TrackGeom<T>& g,
       if constexpr (SMOOTH) {
         const int64_t at = int64_t(r) * a.ld + t;
         const StorePrediction<T> store{b.smooth_state + at, b.smooth_cov + at, a.ld * int64_t(a.max_len)};
-        live = fit_entry<true>(a, g, static_cast<const T*>(nullptr), t, k, lay, valid, m, V, f, bk, bk_stride, store);
+        live = fit_entry<true, kFuseX>(a, g, static_cast<const T*>(nullptr), t, k, lay, valid, m, V, f, bk, bk_stride, store);
       } else {
-        live = fit_entry<true>(a, g, static_cast<const T*>(nullptr), t, k, lay, valid, m, V, f, bk, bk_stride);
+        live = fit_entry<true, kFuseX>(a, g, static_cast<const T*>(nullptr), t, k, lay, valid, m, V, f, bk, bk_stride);
       }
       if (SMOOTH && !live) {
         // the pass stops here: the entries it will not reach get no

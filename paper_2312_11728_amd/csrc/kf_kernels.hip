@@ -179,40 +179,16 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
     f.st |= TRK_BAD_INPUT;
     len = a.max_len;
   }
-  sb.e0[lane] = e0;
+  sb.e0[lane] = int32_t(e0);
   sb.len[lane] = len;
   const int kmax = wave_max(len);
   int k0 = -1;
   bool live = in_range;
-  const int64_t nh = a.n_hits;
   wave_sync();
+  StageRows<J> rows;
+  stage_rows(sb, rows);
   for (int j0 = 0; j0 < kmax; j0 += J) {
-    // All J rows are loaded before any is written to LDS, so the chunk costs
-    // one memory round trip.  A slot past the end of its track loads the
-    // track's last entry instead (an address that is always valid: kmax > 0
-    // means some track has an entry, so n_hits > 0); that slot is never read.
-    int32_t lvr[J];
-    T vr[J][9];
-#pragma unroll
-    for (int r = 0; r < J; ++r) {
-      const int idx = r * 64 + lane;
-      const int l = idx / J, jj = idx % J;
-      const int ln = sb.len[l];
-      const int64_t e = ln > 0 ? sb.e0[l] + min(j0 + jj, ln - 1) : 0;
-      lvr[r] = int32_t(uint16_t(a.hit_layer[e])) | (a.hit_valid[e] ? (1 << 16) : 0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) vr[r][k] = a.hit_pos[k * nh + e];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) vr[r][3 + k] = a.hit_cov[k * nh + e];
-    }
-#pragma unroll
-    for (int r = 0; r < J; ++r) {
-      const int idx = r * 64 + lane;
-      const int l = idx / J, jj = idx % J;
-      sb.lv[jj][l] = lvr[r];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) sb.v[k][jj][l] = vr[r][k];
-    }
+    stage_chunk<1>(a, rows, j0, sb);
     wave_sync();
     const int jn = min(J, kmax - j0);
     for (int jj = 0; jj < jn; ++jj) {
@@ -230,7 +206,7 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
       for (int x = 0; x < 3; ++x) m[x] = sb.v[x][jj][lane];
 #pragma unroll
       for (int x = 0; x < 6; ++x) V[x] = sb.v[3 + x][jj][lane];
-      live = fit_entry<false>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride);
+      live = fit_entry<false, kFuseX>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride);
     }
     wave_sync();   // every lane has read the chunk before the next one is staged
   }

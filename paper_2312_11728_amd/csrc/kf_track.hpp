@@ -170,17 +170,17 @@ KF_HD inline void align_hit(T m[3], const T* __restrict__ sal, int lay, T pos) {
 // the beam axis and a shift a_z along it) and the update.  m is overwritten
 // with the aligned hit.  Returns false when the crossing fails; c2 is the
 // entry's chi2 contribution (0 for a hole).
-template <typename T, typename PreMaterial = NoPreMaterial>
+template <int R2 = kFuseAny, typename T, typename PreMaterial = NoPreMaterial>
 KF_HD inline bool step_forward(T p[6], T c[21], int& q, int j, int lay, int prev, bool valid, T m[3], const T V[6],
                                const TrackGeom<T>& g, const T* __restrict__ sal, T& c2, uint32_t& sst,
                                const PreMaterial& pre = PreMaterial()) {
   const int kind = g.kind[lay];
   if (j > 0) {
-    if (!propagate(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst,
-                   static_cast<T*>(nullptr), static_cast<PropTape<T>*>(nullptr), pre))
+    if (!propagate<R2>(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst,
+                       static_cast<T*>(nullptr), static_cast<PropTape<T>*>(nullptr), pre))
       return false;
   } else {
-    add_material_here(p, c, kind, g.x0[lay], g.mass, sst);
+    add_material_here<R2>(p, c, kind, g.x0[lay], g.mass, sst);
   }
   c2 = T(0);
   if (valid) {
@@ -213,6 +213,7 @@ struct FitState {
   SurfState<T> s;
   T c6[kOnSurface<T> ? 1 : 21];
   int done, prev, nval;
+  int ck_next, ck_slot;   // the next entry with a checkpoint before it, its slot
   uint32_t st;
   T chi2;
 };
@@ -257,6 +258,8 @@ KF_HD inline void start_state(FitState<T>& f, T* bk, int bk_stride, const T p[6]
   f.done = 0;
   f.prev = 0;
   f.nval = 0;
+  f.ck_next = 1;
+  f.ck_slot = 0;
   f.chi2 = T(0);
   if constexpr (kOnSurface<T>) {
     save_full(bk, bk_stride, p, c);
@@ -280,7 +283,7 @@ KF_HD inline void start_state(FitState<T>& f, T* bk, int bk_stride, const T p[6]
 // and leaves it confined to the track's plane.  The 6x6 update has one place,
 // for the first entry and for the lanes that update5 turns away: most waves
 // pass it by.
-template <bool BACK, typename T, typename PreMaterial = NoPreMaterial>
+template <bool BACK, int R2, typename T, typename PreMaterial = NoPreMaterial>
 KF_HD inline bool fit_entry(const FitArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t, int j,
                             int lay, bool valid, T m[3], const T V[6], FitState<T>& f, T* bk, int bk_stride,
                             const PreMaterial& pre = PreMaterial()) {
@@ -291,12 +294,16 @@ KF_HD inline bool fit_entry(const FitArgs<T>& a, const TrackGeom<T>& g, const T*
   if constexpr (!kOnSurface<T>) {
     T* p = f.s.p;
     T* c = f.c6;
-    if (!BACK && a.ckpt && j >= 1 && ((j - 1) % a.seg) == 0) write_checkpoint(a, t, (j - 1) / a.seg, p, c, f.s.q);
+    if (!BACK && a.ckpt && j == f.ck_next) {
+      write_checkpoint(a, t, f.ck_slot, p, c, f.s.q);
+      f.ck_next += a.seg < kMaxLen ? a.seg : kMaxLen;
+      ++f.ck_slot;
+    }
     save_full(bk, bk_stride, p, c);
     const int q = f.s.q;
     uint32_t sst = 0;
     T c2;
-    if (!step_forward(p, c, f.s.q, j, lay, f.prev, valid, m, V, g, sal, c2, sst, pre)) {
+    if (!step_forward<R2>(p, c, f.s.q, j, lay, f.prev, valid, m, V, g, sal, c2, sst, pre)) {
       f.st |= sst;
       return false;
     }
@@ -322,10 +329,12 @@ KF_HD inline bool fit_entry(const FitArgs<T>& a, const TrackGeom<T>& g, const T*
     load_full(bk, bk_stride, s.p, C);
     add_material_here(s.p, C, kind, x0, g.mass, sst);
   } else {
-    if (!BACK && a.ckpt && ((j - 1) % a.seg) == 0) {
+    if (!BACK && a.ckpt && j == f.ck_next) {
       T p[6];
       current_state(f, bk, bk_stride, p, C);
-      write_checkpoint(a, t, (j - 1) / a.seg, p, C, q);
+      write_checkpoint(a, t, f.ck_slot, p, C, q);
+      f.ck_next += a.seg < kMaxLen ? a.seg : kMaxLen;
+      ++f.ck_slot;
     }
     if (f.done == 2) {
 #pragma unroll
@@ -465,7 +474,7 @@ KF_HD inline void fit_track(const FitArgs<T>& a, const TrackGeom<T>& g, const T*
 #pragma unroll
       for (int i = 0; i < 6; ++i) V[i] = V_n[i];
       if (k + 1 < len) acc.load(k + 1, lay_n, valid_n, m_n, V_n);
-      if (!fit_entry<false>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride)) break;
+      if (!fit_entry<false, kFuseY>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride)) break;
     }
   }
   T p[6], c[21];
