@@ -19,75 +19,48 @@
 
 namespace kf {
 
-template <typename T, typename U>
-KF_HD inline void unpack6(const T c[21], U C[6][6]) {
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j < 6; ++j) C[i][j] = c[sym(i, j)];
-}
-
-// packed symmetric adjoint of a full (not necessarily symmetric) adjoint
-template <typename T>
-KF_HD inline void pack6_sym(const T A[6][6], T c[21]) {
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j <= i; ++j) c[sym(i, j)] = T(0.5) * (A[i][j] + A[j][i]);
-}
-
 // Gradient of <Cb, Q(p)> (Cb symmetric full-matrix adjoint, packed) with
-// respect to p, added to pb.  Q as in add_q / highland_var; `seed` selects
-// the incidence of the seed's own layer (radius from the position) instead of
-// the crossing formula (radius = the layer radius, 1/R = rinv).
+// respect to p, added to pb, given the sines and cosines of phi and theta.
+// Q as in add_q / highland_var; `seed` selects the incidence of the seed's own
+// layer (radius from the position) instead of the crossing formula (radius =
+// the layer radius, 1/R = rinv).  The variance is k^2 (ipt sth)^2 one_m xl
+// L^2, so its logarithmic derivatives are 2 by ipt and sth and 1 + 0.076 / L
+// by xl and one_m: no square root, and four reciprocals.
 template <typename T>
-KF_HD inline void q_grad(const T p[6], int kind, T x_over_x0, T mass, bool seed, T rinv, const T cb[21], T pb[6]) {
-  T sph, cph, sth, cth;
-  k_sincos(p[4], &sph, &cph);
-  k_sincos(p[5], &sth, &cth);
-  const T isth = T(1) / sth;
+KF_HD inline void q_grad(const T p[6], T sph, T cph, T sth, T cth, int kind, T x_over_x0, T mass, bool seed, T rinv,
+                         const T cb[21], T pb[6]) {
+  const T isth = k_rcp(sth);
   const T cot = cth * isth;
   const T ipt = p[3];
   const T x = p[0], y = p[1];
-  T A = cph * x + sph * y, r = T(0), ir = rinv;
-  if (seed && kind == 0) {
-    r = k_sqrt(x * x + y * y);
-    ir = T(1) / r;
-  }
+  const T A = cph * x + sph * y;
+  T ir = rinv;
+  if (seed && kind == 0) ir = k_rcp(k_sqrt(x * x + y * y));
   const T ca_raw = (kind == 0) ? sth * A * ir : cth;
   T ca = k_abs(ca_raw);
   const bool clamped = ca < T(kGrazingCos);
   if (clamped) ca = T(kGrazingCos);
+  const T ica = k_rcp(ca);
   const T mis = mass * ipt * sth;
   const T one_m = T(1) + mis * mis;
-  const T xl = x_over_x0 / ca;
-  const T sq = k_sqrt(xl);
-  const T sqm = k_sqrt(one_m);
+  const T xl = x_over_x0 * ica;
   const T Lg = T(1) + T(0.038) * k_log(xl * one_m);
-  const T inv_bp = ipt * sth * sqm;
-  const T th0 = T(0.0136) * inv_bp * sq * Lg;
-  const T var = th0 * th0;
+  // var = ipt v1
+  const T v1 = T(0.0136 * 0.0136) * (ipt * sth * sth) * one_m * xl * (Lg * Lg);
+  const T var = ipt * v1;
+  const T ql = T(1) + T(0.076) * k_rcp(Lg);
   const T ic = ipt * cot;
   const T b33 = cb[sym(3, 3)], b53 = cb[sym(5, 3)], b44 = cb[sym(4, 4)], b55 = cb[sym(5, 5)];
   // Phi = b33 ic^2 var - 2 b53 ic var + b44 var isth^2 + b55 var
   const T bvar = b33 * ic * ic - T(2) * b53 * ic + b44 * isth * isth + b55;
-  const T bic = T(2) * b33 * ic * var - T(2) * b53 * var;
+  const T bic = T(2) * (b33 * ic - b53) * var;
   T bisth = T(2) * b44 * var * isth;
-  T bipt = bic * cot;
-  T bcot = bic * ipt;
-  const T bth0 = T(2) * th0 * bvar;
-  const T binv_bp = bth0 * T(0.0136) * sq * Lg;
-  const T bsq = bth0 * T(0.0136) * inv_bp * Lg;
-  const T bL = bth0 * T(0.0136) * inv_bp * sq;
-  T bxl = bL * T(0.038) / xl + bsq / (T(2) * sq);
-  T bone = bL * T(0.038) / one_m;
-  bipt += binv_bp * sth * sqm;
-  T bsth = binv_bp * ipt * sqm;
-  bone += binv_bp * ipt * sth / (T(2) * sqm);
-  const T bmis = bone * T(2) * mis;
-  bipt += bmis * mass * sth;
-  bsth += bmis * mass * ipt;
-  const T bca = clamped ? T(0) : -bxl * x_over_x0 / (ca * ca);
+  const T bcot = bic * ipt;
+  // d var / d ln ipt = d var / d ln sth = var (2 + 2 ql mis^2 / one_m)
+  const T hv = bvar * (T(2) + T(2) * ql * (mis * mis) * k_rcp(one_m)) * v1;
+  const T bipt = bic * cot + hv;
+  T bsth = hv * ipt * isth;
+  const T bca = clamped ? T(0) : -bvar * var * ql * ica;
   const T bca_raw = ca_raw < T(0) ? -bca : bca;
   T bcth = T(0), bph = T(0), bx = T(0), by = T(0);
   if (kind == 0) {
@@ -118,32 +91,27 @@ KF_HD inline void q_grad(const T p[6], int kind, T x_over_x0, T mass, bool seed,
   pb[5] += bsth * cth - bcth * sth;
 }
 
+// The adjoint Fb of the Jacobian F = G + g d^T, as far as it is used: at the
+// non-trivial elements of G, and contracted with d and g.
+template <typename T>
+struct JacAdjoint {
+  T b03, b04, b13, b14, b25, b43;   // Fb at these elements
+  T bg[6];                          // Fb d (the rows 0, 1, 2 and 4 are used)
+  T bd[6];                          // Fb^T g
+};
+
 // Contribution of <Fb, F(p, s(p))> to pb (total derivative: partials at
 // fixed s plus (d/ds) * ds/dp with ds/dp = tape.d).
 template <typename T>
-KF_HD inline void jacobian_grad(const PropTape<T>& tp, int kind, const T Fb[6][6], T pb[6]) {
+KF_HD inline void jacobian_grad(const PropTape<T>& tp, int kind, const JacAdjoint<T>& ja, T pb[6]) {
   const HelixPt<T>& hp = tp.hp;
   const T s = tp.s, w = tp.w, dwi = tp.dw_dipt, cot = tp.cot, isth = tp.isth, sth = tp.sth, cth = tp.cth;
   const T x = hp.x, y = hp.y, sphm = hp.sphm, cphm = hp.cphm, u = hp.u, shc = hp.shc, ch = hp.ch;
   const T smid = hp.smid, cmid = hp.cmid;
   const T f1 = tp.f1, f2 = tp.f2, inv = tp.inv;
-  const T gv[6] = {cphm, sphm, cot, T(0), w, T(0)};
-  T bG03 = Fb[0][3], bG04 = Fb[0][4], bG13 = Fb[1][3], bG14 = Fb[1][4], bG25 = Fb[2][5], bG43 = Fb[4][3];
-  T bg[6], bd[6];
-#pragma unroll
-  for (int a = 0; a < 6; ++a) {
-    T acc = T(0);
-#pragma unroll
-    for (int b = 0; b < 6; ++b) acc += Fb[a][b] * tp.d[b];
-    bg[a] = acc;
-  }
-#pragma unroll
-  for (int b = 0; b < 6; ++b) {
-    T acc = T(0);
-#pragma unroll
-    for (int a = 0; a < 6; ++a) acc += Fb[a][b] * gv[a];
-    bd[b] = acc;
-  }
+  T bG03 = ja.b03, bG04 = ja.b04, bG13 = ja.b13, bG14 = ja.b14, bG25 = ja.b25, bG43 = ja.b43;
+  const T* bg = ja.bg;
+  const T* bd = ja.bd;
   T bcphm = bg[0], bsphm = bg[1], bcot = bg[2], bw = bg[4];
   T bx = T(0), by = T(0), bs = T(0), bisth = T(0), bsth = T(0), bcth = T(0), bu = T(0), bdx = T(0), bdy = T(0);
   if (kind == 0) {
@@ -183,7 +151,7 @@ KF_HD inline void jacobian_grad(const PropTape<T>& tp, int kind, const T Fb[6][6
   const T bf2 = -bdxdw * s2 * sphm + bdydw * s2 * cphm;
   // f2 = shc^2 / 2; f1'(u) = f2 - 2 f1 / u
   T bshc = bf2 * shc;
-  const T df1 = k_abs(u) < T(1e-3) ? T(1.0 / 6.0) - u * u * T(1.0 / 40.0) : f2 - T(2) * f1 / u;
+  const T df1 = k_abs(u) < T(1e-3) ? T(1.0 / 6.0) - u * u * T(1.0 / 40.0) : f2 - T(2) * f1 * k_rcp(u);
   bu += bf1 * df1;
   // x = x0 + dx, y = y0 + dy
   const T bx0 = bx, by0 = by;
@@ -200,7 +168,7 @@ KF_HD inline void jacobian_grad(const PropTape<T>& tp, int kind, const T Fb[6][6
   bu += bphim;
   T bh = bphimid;
   const T h = T(0.5) * u;
-  const T dsinc = k_abs(h) < T(1e-2) ? -h * T(1.0 / 3.0) + h * h * h * T(1.0 / 30.0) : (ch - shc) / h;
+  const T dsinc = k_abs(h) < T(1e-2) ? -h * T(1.0 / 3.0) + h * h * h * T(1.0 / 30.0) : (ch - shc) * k_rcp(h);
   bh += bshc * dsinc;
   bu += T(0.5) * bh;
   // u = w s, w = dwi ipt
@@ -221,120 +189,66 @@ KF_HD inline void jacobian_grad(const PropTape<T>& tp, int kind, const T Fb[6][6
 }
 
 // Reverse of the update (computed in U), given the predicted state pp, its
-// covariance C (full), the aligned hit m and V.  In: pb, Gb = adjoints of the
-// updated state/covariance (after the charge flip, if it happened).  Out: pb,
-// Gb = adjoints of the predicted state/covariance; mb = adjoint of m.
+// covariance C (packed), the aligned hit m and V.  In: pb, Gb (packed) =
+// adjoints of the updated state/covariance (after the charge flip, if it
+// happened).  Out: pb, Gb = adjoints of the predicted state/covariance; mb =
+// adjoint of m.  With B = C[:, 0:3], K = B S^-1, s = S^-1 r and z = K^T pb:
+//   r-bar = 2 w s + z
+//   S-bar = -(w s s^T + z s^T - K^T Gb K), symmetrised
+//   B-bar = pb s^T - 2 Gb K
+// and C-bar = Gb with S-bar and B-bar put in place, symmetrised.
 template <typename U>
-KF_HD inline void update_vjp(const U pp[6], const U C[6][6], const U m[3], const U V[6], U wchi, U pb[6], U Gb[6][6],
+KF_HD inline void update_vjp(const U pp[6], const U C[21], const U m[3], const U V[6], U wchi, U pb[6], U Gb[21],
                              U mb[3]) {
-  U S[3][3];
+  U Sp[6], Si[6];
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) S[k][l] = C[k][l] + V[sym(k, l)];
-  U Sp[6] = {S[0][0], S[1][0], S[1][1], S[2][0], S[2][1], S[2][2]}, Ip[6];
+  for (int k = 0; k < 6; ++k) Sp[k] = C[k] + V[k];
   uint32_t ist = 0;
-  inverse_checked<U>(Sp, Ip, ist);
-  U Si[3][3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) Si[k][l] = Ip[sym(k, l)];
+  inverse_checked<U>(Sp, Si, ist);
   const U r[3] = {m[0] - pp[0], m[1] - pp[1], m[2] - pp[2]};
-  U K[6][3];
+  U s[3], z[3], K[6][3], GK[6][3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s[k] = Si[sym(k, 0)] * r[0] + Si[sym(k, 1)] * r[1] + Si[sym(k, 2)] * r[2];
 #pragma unroll
   for (int i = 0; i < 6; ++i)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) K[i][k] = C[i][0] * Si[0][k] + C[i][1] * Si[1][k] + C[i][2] * Si[2][k];
-  // flip (sign of the updated ipt) is decided by the caller
-  U Sir[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) Sir[k] = Si[k][0] * r[0] + Si[k][1] * r[1] + Si[k][2] * r[2];
-  U Kb[6][3], rb[3];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) Kb[i][k] = pb[i] * r[k];
+    for (int k = 0; k < 3; ++k)
+      K[i][k] = C[sym(i, 0)] * Si[sym(0, k)] + C[sym(i, 1)] * Si[sym(1, k)] + C[sym(i, 2)] * Si[sym(2, k)];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    U acc = U(2) * wchi * Sir[k];
+    U acc = U(0);
 #pragma unroll
     for (int i = 0; i < 6; ++i) acc += K[i][k] * pb[i];
-    rb[k] = acc;
+    z[k] = acc;
   }
-  // GK = Gb K (6x3), used for B-bar and Si-bar
-  U GK[6][3];
 #pragma unroll
   for (int i = 0; i < 6; ++i)
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       U acc = U(0);
 #pragma unroll
-      for (int j = 0; j < 6; ++j) acc += Gb[i][j] * K[j][k];
+      for (int j = 0; j < 6; ++j) acc += Gb[sym(i, j)] * K[j][k];
       GK[i][k] = acc;
     }
-  // Sib = wchi r r^T + B^T Kb - B^T Gb B  (B = C[:, 0:3])
-  U Sib[3][3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
+  for (int i = 0; i < 6; ++i)
 #pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      U acc = wchi * r[k] * r[l];
+    for (int k = 0; k <= i && k < 3; ++k) {
+      U v = Gb[sym(i, k)] - GK[i][k];
+      if (i < 3) {
+        U n = U(0);   // (K^T Gb K)_ik
 #pragma unroll
-      for (int i = 0; i < 6; ++i) acc += C[i][k] * Kb[i][l];
-      U bgb = U(0);
-#pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        U gbl = U(0);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) gbl += Gb[i][j] * C[j][l];
-        bgb += C[i][k] * gbl;
+        for (int j = 0; j < 6; ++j) n += K[j][i] * GK[j][k];
+        v += n - GK[k][i] - wchi * s[i] * s[k] + U(0.5) * ((pb[i] - z[i]) * s[k] + (pb[k] - z[k]) * s[i]);
+      } else {
+        v += U(0.5) * pb[i] * s[k];
       }
-      Sib[k][l] = acc - bgb;
-    }
-  // Bb = Kb Si - 2 Gb K
-  U Bb[6][3];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-      Bb[i][k] = Kb[i][0] * Si[0][k] + Kb[i][1] * Si[1][k] + Kb[i][2] * Si[2][k] - U(2) * GK[i][k];
-  // Sb = -Si Sib Si
-  U T1[3][3], Sb[3][3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) T1[k][l] = Sib[k][0] * Si[0][l] + Sib[k][1] * Si[1][l] + Sib[k][2] * Si[2][l];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) Sb[k][l] = -(Si[k][0] * T1[0][l] + Si[k][1] * T1[1][l] + Si[k][2] * T1[2][l]);
-  // C-bar = Gb + embed(Sb) + embed(Bb), symmetrised
-  U Cb[6][6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j < 6; ++j) Cb[i][j] = Gb[i][j];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) Cb[k][l] += Sb[k][l];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) Cb[i][k] += Bb[i][k];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j <= i; ++j) {
-      const U v = U(0.5) * (Cb[i][j] + Cb[j][i]);
-      Gb[i][j] = v;
-      Gb[j][i] = v;
+      Gb[sym(i, k)] = v;
     }
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    pb[k] -= rb[k];
-    mb[k] = rb[k];
+    mb[k] = U(2) * wchi * s[k] + z[k];
+    pb[k] -= mb[k];
   }
 }
 
@@ -417,8 +331,6 @@ KF_HD inline void step_vjp(const T p_in[6], const T c_in[21], int q_in, int q_ou
 #pragma unroll
   for (int i = 0; i < 6; ++i) P[i] = p[i];
   hb[0] = hb[1] = hb[2] = R(0);
-  R Gb[6][6];
-  unpack6(cb, Gb);
   if (valid) {
     R m[3] = {m_raw[0], m_raw[1], m_raw[2]};
     R sa = R(0), ca = R(1);
@@ -437,90 +349,113 @@ KF_HD inline void step_vjp(const T p_in[6], const T c_in[21], int q_in, int q_ou
       pb[3] = -pb[3];
 #pragma unroll
       for (int i = 0; i < 6; ++i)
-        if (i != 3) {
-          Gb[3][i] = -Gb[3][i];
-          Gb[i][3] = -Gb[i][3];
-        }
+        if (i != 3) cb[sym(3, i)] = -cb[sym(3, i)];
     }
-    R C[6][6], Vd[6], mb[3];
-    unpack6(c, C);
+    R C[21], Vd[6], mb[3];
+#pragma unroll
+    for (int i = 0; i < 21; ++i) C[i] = c[i];
 #pragma unroll
     for (int i = 0; i < 6; ++i) Vd[i] = V[i];
-    update_vjp<R>(P, C, m, Vd, wchi, pb, Gb, mb);
+    update_vjp<R>(P, C, m, Vd, wchi, pb, cb, mb);
     // m = R(a) h (barrel alignment): h-bar = R^T m-bar
     hb[0] = ca * mb[0] + sa * mb[1];
     hb[1] = -sa * mb[0] + ca * mb[1];
     hb[2] = mb[2];
   }
   // material: C_pred = C_prop + Q(p_pred)
-  R cbp[21];
-  pack6_sym(Gb, cbp);
   if (j > 0) {
-    q_grad<R>(P, kind, R(g.x0[lay]), R(g.mass), false, R(1) / R(g.pos[lay]), cbp, pb);
-    // transport: p = g(p_in), C_prop = F C_in F^T
     const PropTape<R> td = tape_as<R>(tp);
-    R F[6][6];
+    R sph = td.hp.sphm, cph = td.hp.cphm, sth = td.sth, cth = td.cth;
+    if constexpr (sizeof(T) == 4) {   // to the digits of R, not of the tape
+      k_sincos(P[4], &sph, &cph);
+      k_sincos(P[5], &sth, &cth);
+    }
+    q_grad<R>(P, sph, cph, sth, cth, kind, R(g.x0[lay]), R(g.mass), false, k_rcp(R(g.pos[lay])), cb, pb);
+    // Transport: p = g(p_in), C_prop = F C_in F^T, F = G + g d^T.  With Gb the
+    // adjoint of C_prop and GF = Gb F = Gb G + (Gb g) d^T:
+    //   C-bar_in = F^T GF = G^T GF + d e^T, e = GF^T g
+    //   F-bar = 2 GF C_in, at the elements of G and as F-bar d = 2 GF (C_in d)
+    //   and F-bar^T g = 2 C_in e
     const R gv[6] = {td.hp.cphm, td.hp.sphm, td.cot, R(0), td.w, R(0)};
-#pragma unroll
-    for (int a = 0; a < 6; ++a)
-#pragma unroll
-      for (int b = 0; b < 6; ++b) F[a][b] = (a == b ? R(1) : R(0)) + gv[a] * td.d[b];
-    F[0][3] += td.G03;
-    F[0][4] += td.G04;
-    F[1][3] += td.G13;
-    F[1][4] += td.G14;
-    F[2][5] += td.G25;
-    F[4][3] += td.G43;
-    // GF = Gb F; C-bar_in = F^T Gb F; F-bar = 2 Gb F C_in
+    const R* d = td.d;
     R GF[6][6];
 #pragma unroll
-    for (int a = 0; a < 6; ++a)
+    for (int i = 0; i < 6; ++i) {
+      const R b0 = cb[sym(i, 0)], b1 = cb[sym(i, 1)], b2 = cb[sym(i, 2)], b3 = cb[sym(i, 3)], b4 = cb[sym(i, 4)],
+              b5 = cb[sym(i, 5)];
+      const R u = b0 * gv[0] + b1 * gv[1] + b2 * gv[2] + b4 * gv[4];   // (Gb g)_i
+      GF[i][0] = b0 + u * d[0];
+      GF[i][1] = b1 + u * d[1];
+      GF[i][2] = b2 + u * d[2];
+      GF[i][3] = b3 + td.G03 * b0 + td.G13 * b1 + td.G43 * b4 + u * d[3];
+      GF[i][4] = b4 + td.G04 * b0 + td.G14 * b1 + u * d[4];
+      GF[i][5] = b5 + td.G25 * b2 + u * d[5];
+    }
+    R e[6];
 #pragma unroll
-      for (int b = 0; b < 6; ++b) {
-        R acc = R(0);
+    for (int b = 0; b < 6; ++b) e[b] = gv[0] * GF[0][b] + gv[1] * GF[1][b] + gv[2] * GF[2][b] + gv[4] * GF[4][b];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) acc += Gb[a][k] * F[k][b];
-        GF[a][b] = acc;
+    for (int b = 0; b < 6; ++b)
+#pragma unroll
+      for (int a = b; a < 6; ++a) {
+        R v = GF[a][b] + d[a] * e[b];
+        if (a == 3) v += td.G03 * GF[0][b] + td.G13 * GF[1][b] + td.G43 * GF[4][b];
+        if (a == 4) v += td.G04 * GF[0][b] + td.G14 * GF[1][b];
+        if (a == 5) v += td.G25 * GF[2][b];
+        cb[sym(a, b)] = v;
       }
-    R Fb[6][6];
-#pragma unroll
-    for (int a = 0; a < 6; ++a)
-#pragma unroll
-      for (int b = 0; b < 6; ++b) {
-        R acc = R(0);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) acc += GF[a][k] * R(c_in[sym(k, b)]);
-        Fb[a][b] = R(2) * acc;
-      }
-#pragma unroll
-    for (int a = 0; a < 6; ++a)
-#pragma unroll
-      for (int b = 0; b <= a; ++b) {
-        R acc = R(0);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) acc += F[k][a] * GF[k][b];
-        cb[sym(a, b)] = acc;
-      }
-    // p-bar_in = F^T p-bar + d<Fb, F>/dp
-    R pbi[6];
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
+    JacAdjoint<R> ja;
+    auto fb = [&](int a, int b) {   // F-bar at (a, b)
       R acc = R(0);
 #pragma unroll
-      for (int a = 0; a < 6; ++a) acc += F[a][b] * pb[a];
-      pbi[b] = acc;
+      for (int k = 0; k < 6; ++k) acc += GF[a][k] * R(c_in[sym(k, b)]);
+      return R(2) * acc;
+    };
+    ja.b03 = fb(0, 3);
+    ja.b04 = fb(0, 4);
+    ja.b13 = fb(1, 3);
+    ja.b14 = fb(1, 4);
+    ja.b25 = fb(2, 5);
+    ja.b43 = fb(4, 3);
+    R cd[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      R v = R(0), h = R(0);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        v += R(c_in[sym(i, k)]) * d[k];
+        h += R(c_in[sym(i, k)]) * e[k];
+      }
+      cd[i] = v;
+      ja.bd[i] = R(2) * h;
     }
-    jacobian_grad(td, kind, Fb, pbi);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      R v = R(0);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) v += GF[i][k] * cd[k];
+      ja.bg[i] = R(2) * v;
+    }
+    // p-bar_in = F^T p-bar + d<F-bar, F>/dp
+    const R gp = gv[0] * pb[0] + gv[1] * pb[1] + gv[2] * pb[2] + gv[4] * pb[4];
+    R pbi[6];
+    pbi[0] = pb[0] + gp * d[0];
+    pbi[1] = pb[1] + gp * d[1];
+    pbi[2] = pb[2] + gp * d[2];
+    pbi[3] = pb[3] + td.G03 * pb[0] + td.G13 * pb[1] + td.G43 * pb[4] + gp * d[3];
+    pbi[4] = pb[4] + td.G04 * pb[0] + td.G14 * pb[1] + gp * d[4];
+    pbi[5] = pb[5] + td.G25 * pb[2] + gp * d[5];
+    jacobian_grad(td, kind, ja, pbi);
 #pragma unroll
     for (int i = 0; i < 6; ++i) pb[i] = pbi[i];
   } else {
     // the seed's own layer: C = C_in + Q(p_in), p unchanged
-    R Pin[6];
+    R Pin[6], sph, cph, sth, cth;
 #pragma unroll
     for (int i = 0; i < 6; ++i) Pin[i] = p_in[i];
-    q_grad<R>(Pin, kind, R(g.x0[lay]), R(g.mass), true, R(0), cbp, pb);
-#pragma unroll
-    for (int i = 0; i < 21; ++i) cb[i] = cbp[i];
+    k_sincos(Pin[4], &sph, &cph);
+    k_sincos(Pin[5], &sth, &cth);
+    q_grad<R>(Pin, sph, cph, sth, cth, kind, R(g.x0[lay]), R(g.mass), true, R(0), cb, pb);
   }
 }
 
@@ -583,7 +518,6 @@ KF_HD inline void fill_segment(const AdjArgs<T>& a, const TrackGeom<T>& g, const
 #pragma unroll
     for (int i = 0; i < 21; ++i) slot[(6 + i) * n] = c[i];
     slot[27 * n] = T(q);
-    slot[28 * n] = T(prev);
     if (j == jhi) break;
     int lay;
     bool valid;
@@ -615,92 +549,127 @@ KF_HD inline void refill_track(const AdjArgs<T>& a, const TrackGeom<T>& g, const
   }
 }
 
-// Reverse sweep of track t (len entries, the first at e0 of the hit arrays),
-// read through `acc`.
+// Entries, counted from the first valid one, that the forward fit completed
+// on a track it stopped or flagged (a failed crossing, a non-finite step, a
+// bad layer id, or an input it cut short): its steps taken again from the
+// seed.  Any other track completed all of them.
 template <typename T, typename Acc>
-KF_HD inline void adjoint_track(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
-                                const Acc& acc, int len, int64_t e0) {
+KF_HD inline int steps_done(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
+                            const Acc& acc, int k0, int n_steps) {
+  T p[6], c[21];
+  int q, prev;
+  state_before(a, g, sal, t, acc, k0, 0, p, c, q, prev);
+  for (int j = 0; j < n_steps; ++j) {
+    int lay;
+    bool valid;
+    T m[3], V[6];
+    acc.load(k0 + j, lay, valid, m, V);
+    if (lay < 0 || lay >= g.n_layers) return j;
+    if (j == 0) prev = lay;
+    T c2;
+    uint32_t sst = 0;
+    if (!step_forward(p, c, q, j, lay, prev, valid, m, V, g, sal, c2, sst) || !all_finite(p, c, c2)) return j;
+    prev = lay;
+  }
+  return n_steps;
+}
+
+// Whether the forward fit's status says that it may not have completed the track.
+template <typename T>
+KF_HD inline bool was_stopped(const AdjArgs<T>& a, int64_t t) {
+  return a.fwd_status && (a.fwd_status[t] & (TRK_NO_CROSSING | TRK_NONFINITE | TRK_BAD_INPUT));
+}
+
+// The entries of track t (len of them) that a fit uses: k0 the first valid
+// one, n_steps from there.
+template <typename Acc>
+KF_HD inline void fitted_range(const Acc& acc, int len, int max_len, int& k0, int& n_steps) {
+  if (len > max_len) len = max_len;
+  k0 = 0;
+  while (k0 < len && !acc.valid(k0)) ++k0;
+  n_steps = len - k0;
+}
+
+// Reverse sweep over the n_done entries that the forward fit completed of
+// track t (len entries, the first at e0 of the hit arrays), read through
+// `acc`.  STORED: the state before every entry is in the state buffer or (seg
+// = 1) a checkpoint; else it is recomputed from its segment's checkpoint.  The
+// charge after the last completed entry is not needed: the adjoints that a
+// flip there would change sign of are zero.
+template <bool STORED, typename T, typename Acc>
+KF_HD inline void adjoint_sweep(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
+                                const Acc& acc, int len, int64_t e0, int k0, int n_done) {
   const FitArgs<T>& f = a.f;
   const int64_t ld = f.ld, nh = f.n_hits;
-  // hit gradients of this track start at zero (holes, entries beyond max_len
-  // and entries after a stop stay so)
-  for (int k = 0; k < len; ++k) {
-    a.grad_hit[e0 + k] = T(0);
-    a.grad_hit[nh + e0 + k] = T(0);
-    a.grad_hit[2 * nh + e0 + k] = T(0);
-  }
-  if (len > f.max_len) len = f.max_len;
-  int k0 = 0;
-  while (k0 < len && !acc.valid(k0)) ++k0;
-  const int n_steps = len - k0;
-  // entries the forward completed (it stops early on a failed crossing, a
-  // non-finite step or a bad layer id) and the charge after the last one
-  int n_done = n_steps;
-  int q_end = 0;
-  if (n_steps > 0) {
-    const uint32_t stop = TRK_NO_CROSSING | TRK_NONFINITE | TRK_BAD_INPUT;
-    const bool stopped = a.fwd_status && (a.fwd_status[t] & stop);
-    T p[6], c[21];
-    int q, prev;
-    const int j0 = stopped ? 0 : n_steps - 1;
-    state_before(a, g, sal, t, acc, k0, j0, p, c, q, prev);
-    if (stopped) n_done = 0;
-    q_end = q;
-    for (int j = j0; j < n_steps; ++j) {
-      int lay;
-      bool valid;
-      T m[3], V[6];
-      acc.load(k0 + j, lay, valid, m, V);
-      if (lay < 0 || lay >= g.n_layers) break;
-      if (j == 0) prev = lay;
-      T c2;
-      uint32_t sst = 0;
-      if (!step_forward(p, c, q, j, lay, prev, valid, m, V, g, sal, c2, sst)) break;
-      if (!all_finite(p, c, c2)) break;
-      prev = lay;
-      q_end = q;
-      if (stopped) n_done = j + 1;
-    }
-  }
+  const auto hit_grad = [&](int k, const double* h) {
+    const int64_t e = e0 + k;
+    a.grad_hit[e] = T(h[0]);
+    a.grad_hit[nh + e] = T(h[1]);
+    a.grad_hit[2 * nh + e] = T(h[2]);
+  };
+  // entries outside the fit: before the first valid one, past max_len or the
+  // track's stop
+  const double none[3] = {0.0, 0.0, 0.0};
+  for (int k = 0; k < k0 && k < len; ++k) hit_grad(k, none);
+  for (int k = k0 + n_done; k < len; ++k) hit_grad(k, none);
   const double wchi = a.w ? double(a.w[t]) : 1.0;
   double pb[6], cb[21];
 #pragma unroll
   for (int i = 0; i < 6; ++i) pb[i] = 0.0;
 #pragma unroll
   for (int i = 0; i < 21; ++i) cb[i] = 0.0;
-  int q_after = q_end;
+  int q_after = 0;
+  bool last = true;
   for (int j = n_done - 1; j >= 0; --j) {
     T p[6], c[21];
     int q, prev;
-    if (a.seg_buf && j >= 1) {
-      // recomputed by the refill pass
-      const T* slot = a.seg_buf + int64_t(j - 1) * kSegVals * f.n + t;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) p[i] = slot[i * f.n];
-#pragma unroll
-      for (int i = 0; i < 21; ++i) c[i] = slot[(6 + i) * f.n];
-      q = int(slot[27 * f.n]);
-      prev = int(slot[28 * f.n]);
-    } else {
-      state_before(a, g, sal, t, acc, k0, j, p, c, q, prev);
-    }
     int lay;
     bool valid;
     T m[3], V[6];
     acc.load(k0 + j, lay, valid, m, V);
-    if (j == 0) prev = lay;
-    double hb[3];
-    step_vjp(p, c, q, q_after, j, lay, prev, valid, m, V, g, sal, wchi, pb, cb, hb);
-    if (valid) {
-      const int64_t e = e0 + k0 + j;
-      a.grad_hit[e] = T(hb[0]);
-      a.grad_hit[nh + e] = T(hb[1]);
-      a.grad_hit[2 * nh + e] = T(hb[2]);
+    if (STORED && j >= 1) {
+      // slot j - 1 of the buffer the refill pass wrote, or of the checkpoints
+      const int64_t st = a.seg_buf ? f.n : ld * int64_t(f.n_seg);
+      const T* slot = a.seg_buf ? a.seg_buf + int64_t(j - 1) * kSegVals * f.n + t : f.ckpt + int64_t(j - 1) * ld + t;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) p[i] = slot[i * st];
+#pragma unroll
+      for (int i = 0; i < 21; ++i) c[i] = slot[(6 + i) * st];
+      q = int(slot[27 * st]);
+      prev = acc.layer(k0 + j - 1);
+    } else if (STORED) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) p[i] = f.seed_state[i * ld + t];
+#pragma unroll
+      for (int i = 0; i < 21; ++i) c[i] = f.seed_cov[i * ld + t];
+      q = f.seed_charge[t];
+      prev = lay;
+    } else {
+      state_before(a, g, sal, t, acc, k0, j, p, c, q, prev);
+      if (j == 0) prev = lay;
     }
+    double hb[3];
+    step_vjp(p, c, q, last ? q : q_after, j, lay, prev, valid, m, V, g, sal, wchi, pb, cb, hb);
+    hit_grad(k0 + j, hb);   // zero for a hole
     q_after = q;
+    last = false;
   }
 #pragma unroll
   for (int i = 0; i < 6; ++i) a.grad_seed[i * ld + t] = T(pb[i]);
+}
+
+// Reverse pass of track t: the per-track form (host builds, and the device
+// kernel without a state buffer).
+template <typename T, typename Acc>
+KF_HD inline void adjoint_track(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
+                                const Acc& acc, int len, int64_t e0) {
+  int k0, n;
+  fitted_range(acc, len, a.f.max_len, k0, n);
+  if (n > 0 && was_stopped(a, t)) n = steps_done(a, g, sal, t, acc, k0, n);
+  if (a.seg_buf)
+    adjoint_sweep<true>(a, g, sal, t, acc, len, e0, k0, n);
+  else
+    adjoint_sweep<false>(a, g, sal, t, acc, len, e0, k0, n);
 }
 
 }  // namespace kf

@@ -166,7 +166,7 @@ struct AdjArgs {
   // recomputed from its segment's checkpoint when the reverse sweep needs it
   T* seg_buf;
 };
-constexpr int kSegVals = 29;   // state (6), covariance (21), charge, layer of the previous entry
+constexpr int kSegVals = 28;   // state (6), covariance (21), charge
 // blocks of the alignment reduction (kAlignPerBlock entries each)
 constexpr int kAlignPerBlock = 64 * 32;
 inline int64_t adjoint_partial_blocks(int64_t n_hits) { return (n_hits + kAlignPerBlock - 1) / kAlignPerBlock; }

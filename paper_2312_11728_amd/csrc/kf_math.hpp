@@ -366,14 +366,12 @@ KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, b
   if (!near_root(qq, alpha, D, w, lo, best) && !first_root(qq, alpha, D, w, lo, best)) return false;
   // Newton polish on h(s) = r(s)^2 - R^2: two steps (the second matters near
   // tangency, where h'(s) is small and the closed-form root is least
-  // accurate).  In FP32 a correction whose second-order terms stay below a
-  // hundredth of a unit in the last place, (w ds)^2 in the angles and
-  // |w| ds^2 against R in the position, moves the point to first order
-  // (helix_nudge); otherwise, and always in FP64, the point is evaluated
-  // afresh.
+  // accurate).  A correction whose second-order terms stay below a hundredth
+  // of a unit in the last place, (w ds)^2 in the angles and |w| ds^2 against R
+  // in the position, moves the point to first order (helix_nudge); otherwise
+  // the point is evaluated afresh.
   helix_eval(p, sphi, cphi, cot, w, best, hp);
-  constexpr bool kNudge = sizeof(T) == 4;
-  const T tiny = T(0.01 * 1.1920929e-7);
+  const T tiny = T(0.01 * (sizeof(T) == 4 ? 1.1920929e-7 : 2.220446e-16));
 #pragma unroll
   for (int it = 0; it < 2; ++it) {
     const T f = (hp.x * hp.x + hp.y * hp.y - pos * pos);
@@ -382,7 +380,7 @@ KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, b
       const T ds = -f * k_rcp(df);
       best += ds;
       const T wd = w * ds;
-      if (kNudge && wd * wd <= tiny && k_abs(w) * ds * ds <= tiny * pos)
+      if (wd * wd <= tiny && k_abs(w) * ds * ds <= tiny * pos)
         helix_nudge(hp, w, cot, ds);
       else
         helix_eval(p, sphi, cphi, cot, w, best, hp);
@@ -551,9 +549,12 @@ struct NoPreMaterial {
   KF_HD void operator()(const S&...) const {}
 };
 
-template <int R2 = kFuseAny, typename T, typename PreMaterial = NoPreMaterial>
+// No tape.
+struct NoTape {};
+
+template <int R2 = kFuseAny, typename T, typename PreMaterial = NoPreMaterial, typename Tape = NoTape>
 KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool same, bool material, T bz,
-                     T mass, uint32_t& st, T* path = nullptr, PropTape<T>* tape = nullptr,
+                     T mass, uint32_t& st, T* path = nullptr, Tape* tape = static_cast<NoTape*>(nullptr),
                      const PreMaterial& pre = PreMaterial()) {
   const T dw_dipt = -T(q) * T(kCLight) * bz;
   const T w = dw_dipt * p[3];
@@ -600,7 +601,7 @@ KF_HD bool propagate(T p[6], T c[21], int q, int kind, T pos, T x_over_x0, bool 
     d[4] = T(0);
     d[5] = G25 * inv;
   }
-  if (tape) {
+  if constexpr (sizeof(Tape) > sizeof(NoTape)) {
     tape->s = s;
     tape->w = w;
     tape->dw_dipt = dw_dipt;

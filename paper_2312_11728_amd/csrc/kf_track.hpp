@@ -122,6 +122,7 @@ struct CsrTrack {
   const FitArgs<T>& a;
   int64_t e0;
   KF_HD inline bool valid(int k) const { return a.hit_valid[e0 + k] != 0; }
+  KF_HD inline int layer(int k) const { return a.hit_layer[e0 + k]; }
   KF_HD inline void load(int k, int& lay, bool& val, T m[3], T V[6]) const {
     const int64_t e = e0 + k, nh = a.n_hits;
     lay = a.hit_layer[e];
@@ -177,7 +178,7 @@ KF_HD inline bool step_forward(T p[6], T c[21], int& q, int j, int lay, int prev
   const int kind = g.kind[lay];
   if (j > 0) {
     if (!propagate<R2>(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst,
-                       static_cast<T*>(nullptr), static_cast<PropTape<T>*>(nullptr), pre))
+                       static_cast<T*>(nullptr), static_cast<NoTape*>(nullptr), pre))
       return false;
   } else {
     add_material_here<R2>(p, c, kind, g.x0[lay], g.mass, sst);
