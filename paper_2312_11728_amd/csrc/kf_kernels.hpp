@@ -158,7 +158,7 @@ struct AdjArgs {
   T* grad_seed;                // [6][ld]
   T* grad_hit;                 // [3][n_hits]
   T* grad_align;               // [2][n_layers] or null
-  T* partial;                  // [adjoint_partial_blocks(n_hits)][2][kMaxLayers] when grad_align is set
+  T* partial;                  // [2][kMaxLayers][adjoint_partial_blocks(n_hits)] when grad_align is set
   // the states before entries 1 .. max_len - 1 of every track, recomputed
   // segment by segment from the checkpoints by a pass before the reverse
   // sweep ([max_len - 1][kSegVals][n], entry j's state at
