@@ -912,7 +912,7 @@ int kf_score_hits(kf_ctx* ctx, int64_t n, int64_t ld, const float* seed_state, c
   int64_t n_bins = 0;
   for (int l = 0; l <= nl; ++l) t.off[l] = pool_layer_offsets[l];
   for (int l = 0; l < nl; ++l) {
-    int64_t np = 1, nz = 1;
+    int64_t np = g.kind[l] == 0 ? 1 : 0, nz = 1;
     const bool used = pool_layer_offsets[l + 1] > pool_layer_offsets[l];
     if (g.kind[l] == 0 && used) {
       np = std::max<int64_t>(1, int64_t(std::ceil(2.0 * M_PI * geom->pos[l] / kf::kBinArc)));
@@ -927,15 +927,23 @@ int kf_score_hits(kf_ctx* ctx, int64_t n, int64_t ld, const float* seed_state, c
     n_bins += np * nz;
     if (n_bins >= (int64_t(1) << 31)) return fail(KF_ERR_ARG, "too many pool bins (layer %d)", l);
   }
+  if (n_bins == 0) n_bins = 1;   // no layer to search
   // workspace
   const int64_t S = n * prm->beam, P = plan_len;
   auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
+  // (the bins first, at offsets that only the pool and the bin table decide:
+  // reuse_bins finds them there; then, in the same place, the binning's second
+  // copy of the pool and the search's histories, which never live together)
+  const bool buckets = kf::pool_by_buckets(n_pool, n_bins);
+  const int64_t nb = buckets ? kf::pool_buckets(n_bins) : 0;
   const int64_t nsum = n_bins / 2048 + 2;
-  const int64_t b_bins = up(n_bins * 4), b_pool4 = up(n_pool * 4), b_sum = up(nsum * 4) + 256;
-  const int64_t b_pool = up(n_pool * int64_t(sizeof(kf::PoolHit))) + up((n_bins + 1) * 4);
+  const int64_t b_bins = up((buckets ? nb : n_bins) * 4), b_pool4 = up(n_pool * 4);
+  const int64_t b_sum = buckets ? 2 * up((nb + 1) * 4) : b_pool4 + up(nsum * 4) + 256;
+  const int64_t b_hits = up(n_pool * int64_t(sizeof(kf::PoolHit)));
+  const int64_t b_pool = b_hits + up((n_bins + 1) * 4);
   const int64_t b_slot = up(P * S) + 2 * up(P * S * 4) +
                          up(P * int64_t(sizeof(kf::SearchLayer)));
-  const int64_t total = b_bins + 2 * b_pool4 + b_sum + b_pool + b_slot;
+  const int64_t total = b_bins + b_pool4 + b_sum + b_pool + std::max(b_slot, buckets ? b_hits : 0);
   if (size_t(total) > ctx->search_bytes) {
     int prev = 0;
     hipGetDevice(&prev);
@@ -970,13 +978,20 @@ int kf_score_hits(kf_ctx* ctx, int64_t n, int64_t ld, const float* seed_state, c
     return (void*)r;
   };
   kf::SearchWork w;
+  std::memset(&w, 0, sizeof(w));
   w.count = (int32_t*)take(b_bins);
   w.bin_of = (int32_t*)take(b_pool4);
-  w.rank = (int32_t*)take(b_pool4);
-  w.block_sum = (int32_t*)take(up(nsum * 4));
-  w.total = (int32_t*)take(256);
-  w.pool.hits = (kf::PoolHit*)take(up(n_pool * int64_t(sizeof(kf::PoolHit))));
+  if (buckets) {
+    w.bucket_base = (int32_t*)take(up((nb + 1) * 4));
+    w.cursor = (int32_t*)take(up((nb + 1) * 4));
+  } else {
+    w.rank = (int32_t*)take(b_pool4);
+    w.block_sum = (int32_t*)take(up(nsum * 4));
+    w.total = (int32_t*)take(256);
+  }
+  w.pool.hits = (kf::PoolHit*)take(b_hits);
   w.pool.bin_off = (int32_t*)take(up((n_bins + 1) * 4));
+  w.split = (kf::PoolHit*)q;
   kf::SearchArgs a;
   std::memset(&a, 0, sizeof(a));
   a.n = n;

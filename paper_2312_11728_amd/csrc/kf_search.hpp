@@ -53,7 +53,7 @@ constexpr int32_t kStopIdx = -3;
 // Per-layer binning of the hit pool: the hits of layer l sit in bins
 // base[l] + pb * nz[l] + zb, pb in [0, nphi[l]) over phi in [-pi, pi),
 // zb in [0, nz[l]) over z in [lo[l], hi[l]] (hits beyond clamp to the edge
-// bins).  off: the caller's pool CSR by layer.
+// bins).  Disk layers are not searched and have no bins (nphi 0).  off: the caller's pool CSR by layer.
 struct BinTable {
   int32_t n_layers;
   int32_t off[kMaxLayers + 1];
