@@ -5,12 +5,16 @@
 // track is its duplicate, and dup_of[t] names the highest-ranked one.
 //
 // The candidate partners of a track are the tracks that share one of its hit
-// ids: the (hit id, track) pairs of all tracks are sorted by hit id (radix
-// sort).  One thread per (track, layer) finds its hit id's run of pairs by
-// binary search and compares its track's hit list with each outranking
-// partner's, layer by layer; the highest-ranked duplicate of a track is the
-// minimum of a 64-bit rank key over its layers (atomic min).
-#include <hipcub/hipcub.hpp>
+// ids: the (hit id, track) entries of all tracks go into a hash table of
+// linked lists, an entry 16 bytes with all that ranks it, so that a step
+// along a list is one load.  A group of lanes per track, one lane per layer,
+// then walks the lists of its hit ids and compares its track's hit list with
+// each outranking partner's, layer by layer; the highest-ranked duplicate is
+// the minimum of a 64-bit rank key over what the lanes met, whatever the
+// order of the lists.  Bound by launches and the latency of the walk: three
+// kernels, 34 us for 20k tracks of 17 layers (sorting the entries by hit id
+// took 12 to 20 launches and 150 us).
+#include <algorithm>
 
 #include "kf_dedup.hpp"
 
@@ -18,24 +22,44 @@ namespace kf {
 
 namespace {
 
-constexpr uint32_t kNoKey = 0xffffffffu;   // after every hit id (ids are < 2^31)
+// An entry of a list: the next entry's index (-1: the last), the hit id, the
+// track and its score.
+struct alignas(16) DedupNode {
+  int32_t next, hit, track;
+  float score;
+};
 
 __device__ inline bool has_candidate(float s) { return s > -__builtin_huge_valf(); }
 
-// Pair (hit id, track) of entry i = t * n_layers + l; the entries of a track
-// without a candidate and the misses sort last.  Also resets the track's
-// best-duplicate key.
-__global__ void dedup_pairs_kernel(DedupArgs a, uint32_t* keys, int32_t* vals, unsigned long long* best) {
+// heads of the hash table: 2^bits, at least the number of entries
+int table_bits(int64_t m) {
+  int bits = 8;
+  while ((int64_t(1) << bits) < m) ++bits;
+  return bits;
+}
+
+__device__ inline uint32_t slot_of(int32_t h, int bits) {
+  return (uint32_t(h) * 2654435769u) >> (32 - bits);   // 2^32 / golden ratio: neighbouring ids spread
+}
+
+__global__ void __launch_bounds__(256) dedup_clear_kernel(int4* head, int64_t n4) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n4) head[i] = make_int4(-1, -1, -1, -1);
+}
+
+// Entry i = t * n_layers + l into its list, unless it is a miss or its track
+// has no candidate.
+__global__ void __launch_bounds__(256) dedup_insert_kernel(DedupArgs a, DedupNode* node, int32_t* head, int bits) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t m = a.n * a.n_layers;
   if (i >= m) return;
   const int64_t t = i / a.n_layers;
   const int l = int(i - t * a.n_layers);
   const int32_t h = a.hits[t * a.hit_stride + l];
-  const bool has = h >= 0 && has_candidate(a.score[t * a.score_stride]);
-  keys[i] = has ? uint32_t(h) : kNoKey;
-  vals[i] = has ? int32_t(t) : -1;
-  if (l == 0) best[t] = ~0ull;
+  const float s = a.score[t * a.score_stride];
+  if (h < 0 || !has_candidate(s)) return;
+  const int32_t next = atomicExch(&head[slot_of(h, bits)], int32_t(i));
+  node[i] = DedupNode{next, h, int32_t(t), s};
 }
 
 // The rank of track u as an unsigned key: smaller is higher ranked (score
@@ -47,105 +71,100 @@ __device__ inline unsigned long long rank_key(float s, int64_t u) {
   return (static_cast<unsigned long long>(~ord) << 32) | static_cast<uint32_t>(u);
 }
 
-// Entry (t, l): the tracks carrying t's hit id at l that outrank t and are
-// its duplicates; the highest-ranked of them goes to best[t] (atomic min).
-__global__ void dedup_scan_kernel(DedupArgs a, const uint32_t* keys, const int32_t* vals, int64_t m,
-                                  unsigned long long* best) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
+// G lanes per track (a power of two >= n_layers), lane l of the group walking
+// the list of t's hit id at layer l: of the tracks there that outrank t and
+// are its duplicates, the highest-ranked.
+template <int G>
+__global__ void __launch_bounds__(256) dedup_scan_kernel(DedupArgs a, const DedupNode* node, const int32_t* head,
+                                                         int bits) {
+  const int l = int(threadIdx.x) % G;
   const int L = a.n_layers;
-  const int64_t t = i / L;
-  const int l = int(i - t * L);
-  const int32_t* ht = a.hits + t * a.hit_stride;
-  const int32_t h = ht[l];
-  const float st = a.score[t * a.score_stride];
-  if (h < 0 || !has_candidate(st)) return;
-  // first pair with key h
-  int64_t lo = 0, hi = m;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (keys[mid] < uint32_t(h)) lo = mid + 1; else hi = mid;
-  }
-  int nt = -1;
-  unsigned long long mine = ~0ull;
-  for (int64_t j = lo; j < m && keys[j] == uint32_t(h); ++j) {
-    const int64_t u = vals[j];
-    if (u == t) continue;
-    const float su = a.score[u * a.score_stride];
-    if (!(su > st || (su == st && u < t))) continue;   // u does not outrank t
-    const unsigned long long ku = rank_key(su, u);
-    if (ku >= mine) continue;   // ranks below a duplicate found already
-    if (nt < 0) {
-      nt = 0;
-      for (int k = 0; k < L; ++k) nt += ht[k] >= 0 ? 1 : 0;
+  const int64_t stride = int64_t(gridDim.x) * (256 / G);
+  for (int64_t t = (int64_t(blockIdx.x) * 256 + threadIdx.x) / G; t < a.n; t += stride) {   // whole groups
+    const int32_t* ht = a.hits + t * a.hit_stride;
+    const float st = a.score[t * a.score_stride];
+    const bool has = has_candidate(st);
+    const int32_t h = l < L ? ht[l] : -1;
+    unsigned long long mine = ~0ull;
+    if (has && h >= 0) {
+      for (int32_t i = head[slot_of(h, bits)]; i >= 0;) {
+        const DedupNode e = node[i];
+        i = e.next;
+        const int64_t u = e.track;
+        const float su = e.score;
+        if (e.hit != h || u == t) continue;
+        if (!(su > st || (su == st && u < t))) continue;   // u does not outrank t
+        const unsigned long long ku = rank_key(su, u);
+        if (ku >= mine) continue;   // ranks below a duplicate found already
+        const int32_t* hu = a.hits + u * a.hit_stride;
+        // both rows, eight layers' loads at a time (a layer past the last one
+        // repeats it and does not count)
+        int nt = 0, nu = 0, shared = 0;
+        for (int k0 = 0; k0 < L; k0 += 8) {
+          int32_t x[8], y[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const int kk = k0 + k < L ? k0 + k : L - 1;
+            x[k] = ht[kk];
+            y[k] = hu[kk];
+          }
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const bool in = k0 + k < L;
+            nt += (in && x[k] >= 0) ? 1 : 0;
+            nu += (in && y[k] >= 0) ? 1 : 0;
+            shared += (in && y[k] >= 0 && x[k] == y[k]) ? 1 : 0;
+          }
+        }
+        const int nmin = nt < nu ? nt : nu;
+        // exact: a float times an integer <= 64 is exact in double
+        if (shared >= 1 && double(shared) >= double(a.frac) * double(nmin)) mine = ku;
+      }
     }
-    const int32_t* hu = a.hits + u * a.hit_stride;
-    int nu = 0, shared = 0;
-    for (int k = 0; k < L; ++k) {
-      const int32_t x = hu[k];
-      nu += x >= 0 ? 1 : 0;
-      shared += (x >= 0 && x == ht[k]) ? 1 : 0;
+#pragma unroll
+    for (int o = 1; o < G; o <<= 1) {
+      const unsigned long long other = __shfl_xor(mine, o);
+      mine = other < mine ? other : mine;
     }
-    const int nmin = nt < nu ? nt : nu;
-    // exact: a float times an integer <= 64 is exact in double
-    if (shared >= 1 && double(shared) >= double(a.frac) * double(nmin)) mine = ku;
+    if (l == 0) {
+      a.keep[t] = (has && mine == ~0ull) ? 1 : 0;
+      if (a.dup_of) a.dup_of[t] = (has && mine != ~0ull) ? int32_t(uint32_t(mine)) : -1;
+    }
   }
-  if (mine != ~0ull) atomicMin(&best[t], mine);
-}
-
-__global__ void dedup_finish_kernel(DedupArgs a, const unsigned long long* best) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= a.n) return;
-  const bool has = has_candidate(a.score[t * a.score_stride]);
-  const unsigned long long b = best[t];
-  a.keep[t] = (has && b == ~0ull) ? 1 : 0;
-  if (a.dup_of) a.dup_of[t] = (has && b != ~0ull) ? int32_t(uint32_t(b)) : -1;
-}
-
-size_t sort_temp_bytes(int64_t m) {
-  size_t bytes = 0;
-  if (hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, static_cast<const uint32_t*>(nullptr),
-                                         static_cast<uint32_t*>(nullptr), static_cast<const int32_t*>(nullptr),
-                                         static_cast<int32_t*>(nullptr), int(m), 0, 32) != hipSuccess)
-    return 0;
-  return bytes;
 }
 
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+
+template <int G>
+void launch_scan(const DedupArgs& a, const DedupNode* node, const int32_t* head, int bits, hipStream_t s) {
+  const unsigned grid = unsigned(std::min<int64_t>((a.n * G + 255) / 256, 1 << 20));
+  hipLaunchKernelGGL(dedup_scan_kernel<G>, dim3(grid), dim3(256), 0, s, a, node, head, bits);
+}
 
 }  // namespace
 
 size_t dedup_workspace_bytes(int64_t n, int32_t n_layers) {
   const int64_t m = n * n_layers;
-  return 4 * up256(size_t(m) * 4) + up256(size_t(n) * 8) + up256(sort_temp_bytes(m));
+  return up256(size_t(m) * sizeof(DedupNode)) + (size_t(4) << table_bits(m));
 }
 
 hipError_t launch_dedup(const DedupArgs& a, void* work, size_t work_bytes, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   const int64_t m = a.n * a.n_layers;
   if (work_bytes < dedup_workspace_bytes(a.n, a.n_layers)) return hipErrorInvalidValue;
-  char* p = static_cast<char*>(work);
-  uint32_t* k_in = reinterpret_cast<uint32_t*>(p);
-  p += up256(size_t(m) * 4);
-  uint32_t* k_out = reinterpret_cast<uint32_t*>(p);
-  p += up256(size_t(m) * 4);
-  int32_t* v_in = reinterpret_cast<int32_t*>(p);
-  p += up256(size_t(m) * 4);
-  int32_t* v_out = reinterpret_cast<int32_t*>(p);
-  p += up256(size_t(m) * 4);
-  unsigned long long* best = reinterpret_cast<unsigned long long*>(p);
-  p += up256(size_t(a.n) * 8);
-  size_t temp = sort_temp_bytes(m);
-  const unsigned gm = unsigned((m + 255) / 256), gn = unsigned((a.n + 255) / 256);
-  hipLaunchKernelGGL(dedup_pairs_kernel, dim3(gm), dim3(256), 0, s, a, k_in, v_in, best);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = hipcub::DeviceRadixSort::SortPairs(p, temp, k_in, k_out, v_in, v_out, int(m), 0, 32, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dedup_scan_kernel, dim3(gm), dim3(256), 0, s, a, k_out, v_out, m, best);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dedup_finish_kernel, dim3(gn), dim3(256), 0, s, a, best);
+  DedupNode* node = static_cast<DedupNode*>(work);
+  int32_t* head = reinterpret_cast<int32_t*>(static_cast<char*>(work) + up256(size_t(m) * sizeof(DedupNode)));
+  const int bits = table_bits(m);
+  const int64_t n4 = (int64_t(1) << bits) / 4;
+  hipLaunchKernelGGL(dedup_clear_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, s,
+                     reinterpret_cast<int4*>(head), n4);
+  hipLaunchKernelGGL(dedup_insert_kernel, dim3(unsigned((m + 255) / 256)), dim3(256), 0, s, a, node, head, bits);
+  if (a.n_layers <= 16)
+    launch_scan<16>(a, node, head, bits, s);
+  else if (a.n_layers <= 32)
+    launch_scan<32>(a, node, head, bits, s);
+  else
+    launch_scan<64>(a, node, head, bits, s);
   return hipGetLastError();
 }
 
