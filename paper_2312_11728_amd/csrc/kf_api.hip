@@ -1061,17 +1061,17 @@ namespace {
 
 // Sub-buffers of the final fit's workspace, 256-byte aligned.
 struct FinalWork {
-  void *f_state, *f_cov, *f_chi2, *b_state, *b_cov, *b_chi2, *ckpt, *sm_state, *sm_cov, *seed_state, *chi2_work;
+  void *f_state, *f_cov, *f_chi2, *b_state, *b_cov, *b_chi2, *ckpt, *sm_state, *sm_cov, *seed_state;
   int32_t *f_ndf, *b_ndf;
   uint32_t *f_status, *b_status;
   int8_t *f_charge, *b_charge, *seed_charge;
   uint8_t *used, *open;
-  // the sub-batch of the open tracks after the first round
-  int32_t *flag, *len, *pos, *epos, *map, *sub_offsets, *counts;
+  // the sub-batch of the open tracks after the first round; its map and its
+  // counts alternate between the rounds
+  int32_t *map[2], *counts[2], *sub_offsets;
   int16_t* sub_layer;
   uint8_t* sub_used;
-  void *sub_pos, *sub_cov, *scan_temp;
-  size_t scan_bytes;
+  void *sub_pos, *sub_cov;
 };
 
 size_t final_layout(int64_t n, int64_t n_hits, int32_t max_len, size_t esz, unsigned char* base, FinalWork* w) {
@@ -1093,7 +1093,6 @@ size_t final_layout(int64_t n, int64_t n_hits, int32_t max_len, size_t esz, unsi
   x.sm_state = take(6 * N * size_t(max_len) * esz);
   x.sm_cov = take(21 * N * size_t(max_len) * esz);
   x.seed_state = take(6 * N * esz);
-  x.chi2_work = take(size_t(n_hits) * esz);
   x.f_ndf = (int32_t*)take(N * 4);
   x.b_ndf = (int32_t*)take(N * 4);
   x.f_status = (uint32_t*)take(N * 4);
@@ -1103,23 +1102,15 @@ size_t final_layout(int64_t n, int64_t n_hits, int32_t max_len, size_t esz, unsi
   x.seed_charge = (int8_t*)take(N);
   x.used = (uint8_t*)take(size_t(n_hits));
   x.open = (uint8_t*)take(N);
-  x.flag = (int32_t*)take(N * 4);
-  x.len = (int32_t*)take(N * 4);
-  x.pos = (int32_t*)take(N * 4);
-  x.epos = (int32_t*)take(N * 4);
-  x.map = (int32_t*)take(N * 4);
+  for (int i = 0; i < 2; ++i) {
+    x.map[i] = (int32_t*)take(N * 4);
+    x.counts[i] = (int32_t*)take(2 * 4);
+  }
   x.sub_offsets = (int32_t*)take((N + 1) * 4);
-  x.counts = (int32_t*)take(2 * 4);
   x.sub_layer = (int16_t*)take(size_t(n_hits) * 2);
   x.sub_used = (uint8_t*)take(size_t(n_hits));
   x.sub_pos = take(3 * size_t(n_hits) * esz);
   x.sub_cov = take(6 * size_t(n_hits) * esz);
-  // hipCUB's exclusive scan over n int32 (its storage does not depend on T)
-  kf::GatherArgs<float> q{};
-  q.n = n;
-  kf::launch_final_gather(q, nullptr);
-  x.scan_bytes = q.scan_bytes;
-  x.scan_temp = take(x.scan_bytes > 0 ? x.scan_bytes : 1);
   if (w) *w = x;
   return off;
 }
@@ -1129,8 +1120,8 @@ size_t final_layout(int64_t n, int64_t n_hits, int32_t max_len, size_t esz, unsi
 // state after every entry), the backward fit storing its prediction at every
 // entry, the unbiased chi2 of every used hit (entry-parallel) and the
 // round's decisions.
-// The first round runs on the caller's batch.  After each round the tracks
-// still open are gathered, with their used hits, into a compact sub-batch
+// The first round runs on the caller's batch.  Each round's decisions also
+// copy the tracks still open, with their used hits, into a compact sub-batch
 // (the map keeps each one's index in the caller's batch, where the round's
 // decisions and outputs are written), and the host waits for the stream to
 // read their count: the next round is launched on that many tracks only, and
@@ -1157,14 +1148,12 @@ hipError_t final_rounds(kf_ctx* ctx, int pi, int64_t n, int64_t ld, int32_t seed
   r.min_keep = min_keep;
   r.chi2_cut = chi2_cut;
   r.used = w.used;
-  r.open = w.open;
   r.outlier = outlier;
   r.hit_chi2 = (T*)hit_chi2;
-  r.chi2_work = (T*)w.chi2_work;
   r.seed_state = (const T*)w.seed_state;
   r.seed_charge = w.seed_charge;
   r.ckpt = (const T*)w.ckpt;
-  r.pred_state = (const T*)w.sm_state;
+  r.pred_state = (T*)w.sm_state;
   r.pred_cov = (const T*)w.sm_cov;
   r.b_state = (const T*)w.b_state;
   r.b_cov = (const T*)w.b_cov;
@@ -1180,8 +1169,12 @@ hipError_t final_rounds(kf_ctx* ctx, int pi, int64_t n, int64_t ld, int32_t seed
   r.status_out = trk_status;
   r.map = nullptr;
   r.orig_offsets = hit_offsets;
+  r.orig_layer = hit_layer;
+  r.orig_pos = (const T*)hit_pos;
+  r.orig_cov = (const T*)hit_cov;
   r.used_orig = w.used;
   r.open_orig = w.open;
+  r.counts = w.counts[0];
   hipError_t e = kf::launch_final_init(r, s);
   const kf::FitLaunch l = ctx->fit[pi];
   const int32_t n_seg = max_len > 1 ? max_len - 1 : 1;
@@ -1231,36 +1224,21 @@ hipError_t final_rounds(kf_ctx* ctx, int pi, int64_t n, int64_t ld, int32_t seed
     r.round = round;
     e = kf::launch_final_chi2(r, g, s);
     if (e != hipSuccess) break;
+    // the tracks left open go to the next round's sub-batch (the host needs
+    // their count to size the next round's launches)
+    const int alt = round & 1;
+    r.sub_map = round < max_reject ? w.map[alt] : nullptr;
+    r.sub_offsets = w.sub_offsets;
+    r.sub_layer = w.sub_layer;
+    r.sub_used = w.sub_used;
+    r.sub_pos = (T*)w.sub_pos;
+    r.sub_cov = (T*)w.sub_cov;
+    r.counts = w.counts[alt];
+    r.next_counts = w.counts[1 - alt];
     e = kf::launch_final_round(r, s);
     if (e != hipSuccess || round == max_reject) break;
-    // the tracks still open, gathered for the next round (the host needs
-    // their count to size the next round's launches)
-    kf::GatherArgs<T> ga{};
-    ga.n = n;
-    ga.hit_offsets = hit_offsets;
-    ga.hit_layer = hit_layer;
-    ga.used = w.used;
-    ga.hit_pos = (const T*)hit_pos;
-    ga.hit_cov = (const T*)hit_cov;
-    ga.n_hits = n_hits;
-    ga.open = w.open;
-    ga.flag = w.flag;
-    ga.len = w.len;
-    ga.pos = w.pos;
-    ga.epos = w.epos;
-    ga.map = w.map;
-    ga.sub_offsets = w.sub_offsets;
-    ga.sub_layer = w.sub_layer;
-    ga.sub_used = w.sub_used;
-    ga.sub_pos = (T*)w.sub_pos;
-    ga.sub_cov = (T*)w.sub_cov;
-    ga.counts = w.counts;
-    ga.scan_temp = w.scan_temp;
-    ga.scan_bytes = w.scan_bytes;
-    e = kf::launch_final_gather(ga, s);
-    if (e != hipSuccess) break;
     int32_t* counts = ctx->final_counts;
-    e = hipMemcpyAsync(counts, w.counts, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(counts, w.counts[alt], 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess || counts[0] == 0) break;
     nb = counts[0];
@@ -1269,8 +1247,7 @@ hipError_t final_rounds(kf_ctx* ctx, int pi, int64_t n, int64_t ld, int32_t seed
     b_used = w.sub_used;
     b_pos = w.sub_pos;
     b_cov = w.sub_cov;
-    r.open = nullptr;   // every track of the sub-batch is open
-    r.map = w.map;
+    r.map = w.map[alt];
   }
   return e;
 }

@@ -365,41 +365,92 @@ __global__ void __launch_bounds__(kBwdBlock, WAVES) backward_kernel(BwdArgs<T> b
                              sb[threadIdx.x >> 6], bk + threadIdx.x, int(blockDim.x));
 }
 
-// The final fit's unbiased chi2, entry-parallel: thread (r, t) judges hit r
-// of open track t (a used hit) against the estimate from the track's other
-// hits: the forward prediction at r (the filtered state after entry r - 1,
-// from the checkpoints, propagated to r's layer with its material; on the
-// first used entry the seed with that layer's material) combined with the
-// backward pass's prediction there (combine_on_surface), or the forward
-// prediction alone on the last entry and where the backward pass did not
-// reach.  With x, C that estimate, chi2 = r^T (V + H C H^T)^-1 r with
-// r = m - H x (FP64 from here on; NaN when the forward prediction fails or
-// the combination is not positive definite).
+// The final fit's unbiased chi2, entry-parallel: hit r of track t (a used
+// hit) is judged against the estimate from the track's other hits: the
+// forward prediction at r (the filtered state after entry r - 1, from the
+// checkpoints, propagated to r's layer with its material; on the first used
+// entry the seed with that layer's material) combined with the backward
+// pass's prediction there (combine_on_surface), or the forward prediction
+// alone on the last entry and where the backward pass did not reach.  With x,
+// C that estimate, chi2 = r^T (V + H C H^T)^-1 r with r = m - H x (FP64 from
+// here on; NaN when the forward prediction fails or the combination is not
+// positive definite).
+//
+// A block takes J entries of 64 tracks from j0 on and brings them to LDS with
+// consecutive lanes on consecutive entries: read by the lanes that judge them,
+// which are consecutive tracks, every value moved a line of its own (980 MB
+// fetched for 100k tracks of 20 entries, 296 us; now 166 us, of which the
+// states' 440 MB take 90).  J is a cache line of each hit array, or, where
+// that leaves the chip idle, one entry per wave (kChi2Few; 5k open tracks: 10
+// us, 22 with 16 entries a block).  The
+// chi2 takes the place of the backward prediction's x, which its own lane
+// alone has read.
+constexpr int kChi2Block = 256;
 template <typename T>
-__global__ void __launch_bounds__(256, KF_FINAL_CHI2_WAVES) final_chi2_kernel(FinalRoundArgs<T> a, GeomArgs g) {
+constexpr int kChi2Rows = sizeof(T) == 4 ? 16 : 4;   // (8 in FP64 spill)
+constexpr int kChi2FewRows = kChi2Block / 64;
+constexpr int64_t kChi2Few = 64 * 4096;   // entries below which a block takes kChi2FewRows: two rounds of waves
+
+template <typename T, int J>
+struct Chi2Stage {
+  T v[9][J][65];               // hit x, y, z, then the 6 covariance terms
+  int16_t lay[J + 1][64];      // layers, that of entry j0 - 1 first
+  uint8_t used[J][64];
+  int32_t e0[64], len[64], k0[64];        // the tracks' entries, and the first used one
+};
+
+template <typename T, int J>
+__global__ void __launch_bounds__(kChi2Block, KF_FINAL_CHI2_WAVES) final_chi2_kernel(FinalRoundArgs<T> a, GeomArgs g) {
   __shared__ GeomLds<T> sg;
+  __shared__ Chi2Stage<T, J> hs;
   stage_geometry(sg, g);
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int r = int(blockIdx.y);
+  const int tid = int(threadIdx.x), lane = tid & 63;
+  const int64_t t = int64_t(blockIdx.x) * 64 + lane;
+  const int j0 = int(blockIdx.y) * J;
+  if (tid < 64) {
+    int32_t e0 = 0, n_e = 0, k0 = 0;
+    if (t < a.n) {
+      e0 = a.hit_offsets[t];
+      n_e = a.hit_offsets[t + 1] - e0;
+      if (n_e > a.max_len) n_e = a.max_len;
+      while (k0 < n_e && !a.used[int64_t(e0) + k0]) ++k0;
+    }
+    hs.e0[lane] = e0;
+    hs.len[lane] = n_e;
+    hs.k0[lane] = k0;
+  }
+  __syncthreads();
+  const int64_t nh = a.n_hits;
+#pragma unroll
+  for (int i = 0; i < J * 64 / kChi2Block; ++i) {
+    const int row = i * kChi2Block + tid, l = row / J, jj = row % J;
+    const int k = j0 + jj;
+    if (k < hs.len[l]) {
+      const int64_t e = int64_t(hs.e0[l]) + k;
+      hs.used[jj][l] = a.used[e];
+      hs.lay[jj + 1][l] = a.hit_layer[e];
+      if (jj == 0 && k > 0) hs.lay[0][l] = a.hit_layer[e - 1];
+#pragma unroll
+      for (int x = 0; x < 3; ++x) hs.v[x][jj][l] = a.hit_pos[x * nh + e];
+#pragma unroll
+      for (int x = 0; x < 6; ++x) hs.v[3 + x][jj][l] = a.hit_cov[x * nh + e];
+    }
+  }
+  __syncthreads();
   if (t >= a.n) return;
-  if (a.open && !(a.open[t] & kFinalOpen)) return;
-  const int64_t e0 = a.hit_offsets[t];
-  int n_e = int(a.hit_offsets[t + 1] - e0);
-  if (n_e > a.max_len) n_e = a.max_len;
-  if (r >= n_e) return;
-  const int64_t e = e0 + r;
-  if (!a.used[e]) return;
-  T res = k_nan<T>();
-  if (!(a.b_status[t] & TRK_BAD_INPUT)) {
-    int k0 = 0;
-    while (k0 < r && !a.used[e0 + k0]) ++k0;
-    const int lay = a.hit_layer[e];
-    if (lay >= 0 && lay < g.n_layers) {
+  const int n_e = hs.len[lane], k0 = hs.k0[lane];
+  const bool refitted = !(a.b_status[t] & TRK_BAD_INPUT);
+  const int64_t os = a.n * int64_t(a.max_len);
+  const auto judge = [&](int jj) {
+    const int r = j0 + jj;
+    if (r >= n_e || !hs.used[jj][lane]) return;
+    const int64_t at = int64_t(r) * a.n + t;
+    const int lay = hs.lay[jj + 1][lane];
+    T res = k_nan<T>();
+    if (refitted && lay >= 0 && lay < g.n_layers) {
       const int kind = sg.kind[lay];
       const T pos = sg.pos[lay], x0 = sg.x0[lay];
-      // what the entry reads besides the forward prediction (the backward
-      // prediction, the hit), loaded before the prediction is computed
-      const int64_t os = a.n * int64_t(a.max_len), at = int64_t(r) * a.n + t;
+      // the backward prediction, loaded before the forward one is computed
       const bool two = r < n_e - 1;
       T pb[6], cb[21];
       if (two) {
@@ -408,12 +459,6 @@ __global__ void __launch_bounds__(256, KF_FINAL_CHI2_WAVES) final_chi2_kernel(Fi
 #pragma unroll
         for (int i = 0; i < 21; ++i) cb[i] = a.pred_cov[i * os + at];
       }
-      const int64_t nh = a.n_hits;
-      T hm[3], hv[6];
-#pragma unroll
-      for (int i = 0; i < 3; ++i) hm[i] = a.hit_pos[i * nh + e];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) hv[i] = a.hit_cov[i * nh + e];
       T p[6], c[21];
       int q;
       uint32_t st = 0;
@@ -432,7 +477,7 @@ __global__ void __launch_bounds__(256, KF_FINAL_CHI2_WAVES) final_chi2_kernel(Fi
 #pragma unroll
         for (int i = 0; i < 21; ++i) c[i] = f[(6 + i) * cs];
         q = int(f[27 * cs]);
-        const int prev = a.hit_layer[e - 1];
+        const int prev = hs.lay[jj][lane];
         ok = propagate(p, c, q, kind, pos, x0, lay == prev, true, T(g.bz), T(g.mass), st);
       }
       if (ok) {
@@ -449,15 +494,15 @@ __global__ void __launch_bounds__(256, KF_FINAL_CHI2_WAVES) final_chi2_kernel(Fi
           for (int i = 0; i < 21; ++i) cx[i] = c[i];
         }
         if (ok) {
-          const double r0 = double(hm[0]) - double(px[0]);
-          const double r1 = double(hm[1]) - double(px[1]);
-          const double r2 = double(hm[2]) - double(px[2]);
-          const double sa = double(hv[0]) + double(cx[0]);
-          const double sb = double(hv[1]) + double(cx[1]);
-          const double sc = double(hv[2]) + double(cx[2]);
-          const double sd = double(hv[3]) + double(cx[3]);
-          const double se = double(hv[4]) + double(cx[4]);
-          const double sf = double(hv[5]) + double(cx[5]);
+          const double r0 = double(hs.v[0][jj][lane]) - double(px[0]);
+          const double r1 = double(hs.v[1][jj][lane]) - double(px[1]);
+          const double r2 = double(hs.v[2][jj][lane]) - double(px[2]);
+          const double sa = double(hs.v[3][jj][lane]) + double(cx[0]);
+          const double sb = double(hs.v[4][jj][lane]) + double(cx[1]);
+          const double sc = double(hs.v[5][jj][lane]) + double(cx[2]);
+          const double sd = double(hs.v[6][jj][lane]) + double(cx[3]);
+          const double se = double(hs.v[7][jj][lane]) + double(cx[4]);
+          const double sf = double(hs.v[8][jj][lane]) + double(cx[5]);
           const double i00 = sc * sf - se * se, i10 = sd * se - sb * sf, i20 = sb * se - sc * sd;
           const double i11 = sa * sf - sd * sd, i21 = sb * sd - sa * se, i22 = sa * sc - sb * sb;
           const double det = sa * i00 + sb * i10 + sd * i20;
@@ -467,8 +512,14 @@ __global__ void __launch_bounds__(256, KF_FINAL_CHI2_WAVES) final_chi2_kernel(Fi
         }
       }
     }
+    a.pred_state[at] = res;
+  };
+  if constexpr (J == kChi2Block / 64) {
+    judge(tid >> 6);
+  } else {
+#pragma unroll 1
+    for (int jj = tid >> 6; jj < J; jj += kChi2Block / 64) judge(jj);
   }
-  a.chi2_work[e] = res;
 }
 
 }  // namespace
@@ -504,8 +555,14 @@ hipError_t launch_backward_predictions(const BwdArgs<T>& a, const GeomArgs& g, h
 template <typename T>
 hipError_t launch_final_chi2(const FinalRoundArgs<T>& a, const GeomArgs& g, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(final_chi2_kernel<T>, dim3(unsigned((a.n + 255) / 256), unsigned(a.max_len)), dim3(256), 0, s,
-                     a, g);
+  const unsigned tiles = unsigned((a.n + 63) / 64);
+  const auto rows = [&](int j) { return unsigned((a.max_len + j - 1) / j); };
+  if (a.n * a.max_len <= kChi2Few)
+    hipLaunchKernelGGL((final_chi2_kernel<T, kChi2FewRows>), dim3(tiles, rows(kChi2FewRows)), dim3(kChi2Block), 0, s, a,
+                       g);
+  else
+    hipLaunchKernelGGL((final_chi2_kernel<T, kChi2Rows<T>>), dim3(tiles, rows(kChi2Rows<T>)), dim3(kChi2Block), 0, s, a,
+                       g);
   return hipGetLastError();
 }
 
