@@ -458,7 +458,7 @@ __global__ void __launch_bounds__(kSearchBlock, kSearchWaves) search_kernel(Sear
     const bool open = slot && extend_open<B>(a, X, L, layers[step > 0 ? step - 1 : 0], step, s, i, k, score, w, st);
     Kids<B> K;
     kids_init(K);
-    scan_window<B>(a, L, w, k.p, k.c, score, K, st);
+    scan_window<B>(a, X, L, w, i, k.p, k.c, score, K, st);
     if (open) extend_close<B>(a, X, i, k, score, K);
     if (st) atomicOr(&a.status[s / a.beam], st);
     __syncthreads();
