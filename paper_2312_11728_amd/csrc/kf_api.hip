@@ -780,7 +780,7 @@ int kf_reserve(kf_ctx* ctx, int64_t max_tracks, int32_t max_len) {
   auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
   const int64_t b_hist = up(int64_t(kf::kMaxLen + 2) * 4), b_order = up(max_tracks * 4);
   const int64_t b_tiles = up((n_tiles + 1) * 8), b_lv = up(cap * 4), b_hit = up(cap * 9 * 8);
-  const int64_t total = 2 * b_hist + 2 * b_order + b_tiles + b_lv + b_hit;
+  const int64_t total = 2 * b_hist + b_order + b_tiles + b_lv + b_hit;
   hipError_t e = hipMalloc(&ctx->work_mem, size_t(total));
   hipSetDevice(prev);
   if (e != hipSuccess) {
@@ -794,8 +794,6 @@ int kf_reserve(kf_ctx* ctx, int64_t max_tracks, int32_t max_len) {
   w.cursor = (int32_t*)p;
   p += b_hist;
   w.order = (int32_t*)p;
-  p += b_order;
-  w.slot_of = (int32_t*)p;
   p += b_order;
   w.tile_base = (int64_t*)p;
   p += b_tiles;

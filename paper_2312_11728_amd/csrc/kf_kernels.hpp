@@ -117,7 +117,6 @@ struct PackWork {
   int32_t* hist;       // [kMaxLen + 2] per-length counts, then cursors
   int32_t* cursor;     // [kMaxLen + 2]
   int32_t* order;      // [max_tracks] slot -> track
-  int32_t* slot_of;    // [max_tracks] track -> slot
   int64_t* tile_base;  // [max_tiles + 1]
   int32_t* lv;         // [cap]
   void* hit;           // [9][cap] of float or double
