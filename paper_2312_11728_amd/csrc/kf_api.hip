@@ -815,7 +815,7 @@ int kf_set_fit_launch(kf_ctx* ctx, kf_precision prec, int32_t block, int32_t per
   if (persistent != 0 && persistent != 1) return fail(KF_ERR_ARG, "persistent must be 0 or 1");
   if (blocks_per_cu < 1 || blocks_per_cu > 32) return fail(KF_ERR_ARG, "blocks_per_cu = %d outside [1, 32]", blocks_per_cu);
   KF_REQUIRE(ctx);
-  ctx->fit[prec == KF_F32 ? 0 : 1] = kf::FitLaunch{block, persistent, blocks_per_cu, waves, layout};
+  ctx->fit[prec == KF_F32 ? 0 : 1] = kf::FitLaunch{block, persistent, blocks_per_cu, waves, layout, 1};
   return ok();
 }
 

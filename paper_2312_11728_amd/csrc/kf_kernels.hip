@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(kFitBlock, WAVES) fit_persistent_kernel(FitArg
 // Forward fit of the tracks in slots [w0, w0 + 64) (one wave; slot i holds
 // track order[i] when sorted, else track i; slots >= n hold no track).  Every
 // lane of the wave must call it.
-template <typename T, int J, bool SORTED>
+template <typename T, int J, bool SORTED, int R2>
 __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t w0,
                                 StageBuf<T, J>& sb, T* bk, int bk_stride) {
   static_assert((J & (J - 1)) == 0 && J <= 64, "J must be a power of two <= 64");
@@ -206,7 +206,7 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
       for (int x = 0; x < 3; ++x) m[x] = sb.v[x][jj][lane];
 #pragma unroll
       for (int x = 0; x < 6; ++x) V[x] = sb.v[3 + x][jj][lane];
-      live = fit_entry<false, kFuseX>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride);
+      live = fit_entry<false, R2>(a, g, sal, t, k - k0, lay, valid, m, V, f, bk, bk_stride);
     }
     wave_sync();   // every lane has read the chunk before the next one is staged
   }
@@ -238,7 +238,7 @@ __device__ __forceinline__ int64_t run_order(int64_t block, int64_t n_blocks, in
   return (set * kXcds + r % kXcds) * per + r / kXcds;
 }
 
-template <typename T, int WAVES, bool SORTED>
+template <typename T, int WAVES, bool SORTED, int R2 = kFuseX>
 __global__ void __launch_bounds__(kFitBlock, WAVES) fit_staged_kernel(FitArgs<T> a, GeomArgs g) {
   constexpr int J = stage_entries<T, WAVES>();
   __shared__ GeomLds<T> sg;
@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(kFitBlock, WAVES) fit_staged_kernel(FitArgs<T>
   stage_geometry(sg, g);
   const int64_t block = SORTED ? run_order(blockIdx.x, gridDim.x, int(blockDim.x)) : int64_t(blockIdx.x);
   const int64_t w0 = block * blockDim.x + (threadIdx.x & ~63u);
-  fit_wave_staged<T, J, SORTED>(a, TrackGeom<T>{sg.kind, sg.pos, sg.x0, g.n_layers, T(g.bz), T(g.mass)},
+  fit_wave_staged<T, J, SORTED, R2>(a, TrackGeom<T>{sg.kind, sg.pos, sg.x0, g.n_layers, T(g.bz), T(g.mass)},
                                 a.align ? sal : nullptr, w0, sb[threadIdx.x >> 6], bk + threadIdx.x,
                                 int(blockDim.x));
 }
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(kFitBlock, WAVES) fit_staged_persistent_kernel
     __syncthreads();
     if (my >= a.n_tiles) break;
     const int64_t w0 = my * blockDim.x + (threadIdx.x & ~63u);
-    fit_wave_staged<T, J, SORTED>(a, TrackGeom<T>{sg.kind, sg.pos, sg.x0, g.n_layers, T(g.bz), T(g.mass)},
+    fit_wave_staged<T, J, SORTED, kFuseX>(a, TrackGeom<T>{sg.kind, sg.pos, sg.x0, g.n_layers, T(g.bz), T(g.mass)},
                                   a.align ? sal : nullptr, w0, sb[threadIdx.x >> 6], bk + threadIdx.x,
                                   int(blockDim.x));
   }
@@ -603,9 +603,29 @@ hipError_t launch_fit_w(const FitArgs<T>& a, const GeomArgs& g, const FitLaunch&
   return hipGetLastError();
 }
 
+// The launch of a caller that chose none: results to the bit those of layout
+// 0.  FP32: the staged kernel, compiled with that layout's rounding (20
+// entries, direct / staged: 64 to 16k tracks 73 / 71 us, 48k 88 / 81, 64k 153 /
+// 85, 128k 295 / 115: the direct reads' cache lines no longer stay in the
+// caches).  FP64: the direct kernel, whose rounding the staged one does not
+// have on disks.  Blocks of one wave while every wave then has a compute unit
+// to itself (16k tracks FP32 74 us with blocks of 256, 72 with 64, FP64 89 and
+// 84; beyond, a staging block's LDS would leave the chip half empty).
+template <typename T>
+hipError_t launch_fit_default(const FitArgs<T>& a, const GeomArgs& g, int n_cu, hipStream_t s) {
+  const int block = (a.n + 63) / 64 <= n_cu ? 64 : 256;
+  const dim3 grid(unsigned((a.n + block - 1) / block));
+  if constexpr (sizeof(T) == 4)
+    hipLaunchKernelGGL((fit_staged_kernel<T, 2, false, kFuseY>), grid, dim3(block), 0, s, a, g);
+  else
+    hipLaunchKernelGGL((fit_kernel<T, 1, 0>), grid, dim3(block), 0, s, a, g);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_fit(const FitArgs<T>& a, const GeomArgs& g, const FitLaunch& l, int n_cu, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
+  if (!l.chosen) return launch_fit_default(a, g, n_cu, s);
   if (a.packed == 4) return l.waves == 2 ? launch_fit_w<T, 2, 4>(a, g, l, n_cu, s) : launch_fit_w<T, 1, 4>(a, g, l, n_cu, s);
   if (a.packed == 3) return l.waves == 2 ? launch_fit_w<T, 2, 3>(a, g, l, n_cu, s) : launch_fit_w<T, 1, 3>(a, g, l, n_cu, s);
   if (a.packed == 2) return l.waves == 2 ? launch_fit_w<T, 2, 2>(a, g, l, n_cu, s) : launch_fit_w<T, 1, 2>(a, g, l, n_cu, s);

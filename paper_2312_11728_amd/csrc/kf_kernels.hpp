@@ -144,6 +144,7 @@ struct FitLaunch {
   int waves;        // register budget: at least this many waves per SIMD (1 or 2)
   int layout;       // 0 CSR, 1 length-sorted CSR, 2 length-sorted packed, 3 LDS-staged CSR,
                     // 4 LDS-staged length-sorted CSR (1, 2, 4 need a workspace)
+  int chosen = 0;   // set by the caller; else launch_fit picks the kernel by size
 };
 template <typename T>
 hipError_t launch_fit(const FitArgs<T>& a, const GeomArgs& g, const FitLaunch& l, int n_cu, hipStream_t s);
