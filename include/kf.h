@@ -180,7 +180,7 @@ int kf_update(kf_ctx *ctx, kf_precision prec, int64_t n, int64_t ld,
  * Layout (a tuning choice, see kf_set_fit_launch): with a workspace from
  * kf_reserve large enough for n tracks and max_len, the call can first sort
  * the tracks by entry count (longest first, so that the lanes of a wave run
- * similar loops) and optionally copy the hits into a tile-transposed layout
+ * similar loops; layout 4: within groups of 2048 consecutive tracks) and optionally copy the hits into a tile-transposed layout
  * (entry k of 64 tracks contiguous, every hit load of a wave one coalesced
  * read); the fit can also stage the CSR entries of each wave's 64 tracks
  * through LDS itself, a few entries per track at a time (no pass before the
@@ -630,7 +630,9 @@ int kf_reserve(kf_ctx *ctx, int64_t max_tracks, int32_t max_len);
  * compiler fuses different multiply-adds, so across them results agree to
  * rounding (FP64: about 1e-12 relative) and each meets the same accuracy
  * against the FP64 reference.  The choice is made by the autotuner of the
- * Python package for speed.  Stored in the context. */
+ * Python package for speed.  Stored in the context.  Until it is set the
+ * library picks the kernel by precision and size, with the bits of layout 0;
+ * kf_get_fit_launch then reports 256, 0, 4, 1, 0. */
 int kf_set_fit_launch(kf_ctx *ctx, kf_precision prec, int32_t block, int32_t persistent, int32_t blocks_per_cu,
                       int32_t waves, int32_t layout);
 int kf_get_fit_launch(const kf_ctx *ctx, kf_precision prec, int32_t *block, int32_t *persistent,

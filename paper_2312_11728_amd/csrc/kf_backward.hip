@@ -378,13 +378,12 @@ __global__ void __launch_bounds__(kBwdBlock, WAVES) backward_kernel(BwdArgs<T> b
 //
 // A block takes J entries of 64 tracks from j0 on and brings them to LDS with
 // consecutive lanes on consecutive entries: read by the lanes that judge them,
-// which are consecutive tracks, every value moved a line of its own (980 MB
-// fetched for 100k tracks of 20 entries, 296 us; now 166 us, of which the
+// which are consecutive tracks, every value moved a line of its own (100k
+// tracks of 20 entries: 2.0 GB fetched, 296 us; now 166 us, of which the
 // states' 440 MB take 90).  J is a cache line of each hit array, or, where
 // that leaves the chip idle, one entry per wave (kChi2Few; 5k open tracks: 10
-// us, 22 with 16 entries a block).  The
-// chi2 takes the place of the backward prediction's x, which its own lane
-// alone has read.
+// us, 22 with 16 entries a block).  The chi2 takes the place of the backward
+// prediction's x, which its own lane alone has read.
 constexpr int kChi2Block = 256;
 template <typename T>
 constexpr int kChi2Rows = sizeof(T) == 4 ? 16 : 4;   // (8 in FP64 spill)

@@ -224,9 +224,9 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
 // the same time and behind one L2.  Blocks go to the kXcds dies in turn, so
 // the blocks of kXcds groups are dealt out in turn too: block r of them to
 // group r % kXcds (a permutation of the blocks; a last incomplete set of
-// groups keeps its order).  500k tracks of 3 to 26 entries, FP32: 333
-// us, from 451 sorted as a whole (1.2 GB fetched for 260 MB of hits).  Groups of
-// 8192 take as long.
+// groups keeps its order).  500k tracks of 3 to 26 entries, FP32: 333 us, from
+// 451 sorted as a whole (1.0 GB fetched, from 2.4, for 250 MB of hits).  Groups
+// of 8192 take as long.
 constexpr int kOrderGroup = 2048;
 constexpr int kXcds = 8;
 
