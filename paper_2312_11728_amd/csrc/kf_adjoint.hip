@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(64) align_partial_kernel(AdjArgs<T> a, GeomArg
     for (int u = 0; u < kAhead; ++u) {
       const int64_t e = b0 + int64_t(k + u) * 64 + lane;
       use[u] = e < last;
-      const int64_t ee = use[u] ? e : first;
+      const int64_t ee = align_load_entry(e, last);
       use[u] = use[u] && a.f.hit_valid[ee] != 0;
       lay[u] = a.f.hit_layer[ee];
       hx[u] = a.f.hit_pos[ee];

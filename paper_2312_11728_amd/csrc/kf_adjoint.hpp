@@ -295,6 +295,12 @@ KF_HD inline PropTape<U> tape_as(const PropTape<T>& t) {
   return o;
 }
 
+// The entry that a lane of the alignment reduction loads for place e of a batch
+// whose entries end before `last`, in arrays of at least one entry.  Past the
+// end it is entry 0, not the batch's first: a batch of empty tracks at the end
+// of the arrays has none.
+KF_HD inline int64_t align_load_entry(int64_t e, int64_t last) { return e < last ? e : 0; }
+
 // Adjoint of one entry (see the file comment).  p_in, c_in, q_in: the state
 // entering the entry (recomputed in the forward path's type T, so the
 // transport, crossing and flip decisions are the forward's own); q_out: the
