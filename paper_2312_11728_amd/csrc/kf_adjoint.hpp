@@ -302,12 +302,15 @@ KF_HD inline PropTape<U> tape_as(const PropTape<T>& t) {
 KF_HD inline int64_t align_load_entry(int64_t e, int64_t last) { return e < last ? e : 0; }
 
 // Adjoint of one entry (see the file comment).  p_in, c_in, q_in: the state
-// entering the entry (recomputed in the forward path's type T, so the
-// transport, crossing and flip decisions are the forward's own); q_out: the
-// charge after the entry (it differs from q_in iff the update flipped it);
-// m_raw: the hit before alignment.  pb, cb: in, adjoints of the state leaving
-// the entry; out, adjoints of the state entering it.  hb: adjoint of the raw
-// hit position.  The reverse arithmetic runs in FP64 for both precisions: the
+// entering the entry; q_out: the charge after the entry (it differs from q_in
+// iff the update flipped it); m_raw: the hit before alignment.  pb, cb: in,
+// adjoints of the state leaving the entry; out, adjoints of the state entering
+// it.  hb: adjoint of the raw hit position.  The transport is retaken in the
+// forward path's type T; in FP64 the forward fit takes it on the surface frame
+// and rounds it differently, so that at a tangent crossing one may find a path
+// where the other finds none.  Without one here the entry passes nothing back:
+// hb, pb and cb are zero, and the entries before it are swept on their own.
+// The reverse arithmetic runs in FP64 for both precisions: the
 // covariance adjoint is of order 1/sigma^4 of the hits while the gradient
 // with respect to the earlier states is of order one, so the products in the
 // transport and update reverse cancel by five to six orders of magnitude,
@@ -326,9 +329,16 @@ KF_HD inline void step_vjp(const T p_in[6], const T c_in[21], int q_in, int q_ou
   int q = q_in;
   uint32_t sst = 0;
   PropTape<T> tp;
+  hb[0] = hb[1] = hb[2] = R(0);
   if (j > 0) {
-    propagate(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst, static_cast<T*>(nullptr),
-              &tp);
+    if (!propagate(p, c, q, kind, g.pos[lay], g.x0[lay], lay == prev, true, g.bz, g.mass, sst,
+                   static_cast<T*>(nullptr), &tp)) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) pb[i] = R(0);
+#pragma unroll
+      for (int i = 0; i < 21; ++i) cb[i] = R(0);
+      return;
+    }
   } else {
     add_material_here(p, c, kind, g.x0[lay], g.mass, sst);
   }
@@ -336,7 +346,6 @@ KF_HD inline void step_vjp(const T p_in[6], const T c_in[21], int q_in, int q_ou
   R P[6];
 #pragma unroll
   for (int i = 0; i < 6; ++i) P[i] = p[i];
-  hb[0] = hb[1] = hb[2] = R(0);
   if (valid) {
     R m[3] = {m_raw[0], m_raw[1], m_raw[2]};
     R sa = R(0), ca = R(1);
