@@ -567,24 +567,23 @@ KF_HD inline void refill_track(const AdjArgs<T>& a, const TrackGeom<T>& g, const
 // Entries, counted from the first valid one, that the forward fit completed
 // on a track it stopped or flagged (a failed crossing, a non-finite step, a
 // bad layer id, or an input it cut short): its steps taken again from the
-// seed.  Any other track completed all of them.
+// seed, in the fit's own form.  The 6x6 form of step_vjp() may round a tangent
+// crossing to the other side in FP64 and count an entry whose states the fit
+// never wrote.  Any other track completed all of them.
 template <typename T, typename Acc>
 KF_HD inline int steps_done(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
                             const Acc& acc, int k0, int n_steps) {
-  T p[6], c[21];
-  int q, prev;
-  state_before(a, g, sal, t, acc, k0, 0, p, c, q, prev);
+  FitArgs<T> fa = a.f;
+  fa.ckpt = nullptr;   // read here, not written again
+  FitState<T> f;
+  T bk[28];
+  begin_fit(fa, t, g.bz, f, bk, 1);
   for (int j = 0; j < n_steps; ++j) {
     int lay;
     bool valid;
     T m[3], V[6];
     acc.load(k0 + j, lay, valid, m, V);
-    if (lay < 0 || lay >= g.n_layers) return j;
-    if (j == 0) prev = lay;
-    T c2;
-    uint32_t sst = 0;
-    if (!step_forward(p, c, q, j, lay, prev, valid, m, V, g, sal, c2, sst) || !all_finite(p, c, c2)) return j;
-    prev = lay;
+    if (!fit_entry<false, kFuseAny>(fa, g, sal, t, j, lay, valid, m, V, f, bk, 1)) return j;
   }
   return n_steps;
 }

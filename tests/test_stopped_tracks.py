@@ -20,7 +20,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["step"])
+@pytest.mark.parametrize("check", ["step", "done"])
 def test_stops(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr[-2000:]
