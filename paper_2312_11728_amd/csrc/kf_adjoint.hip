@@ -250,7 +250,7 @@ __device__ void refill_wave_staged(const AdjArgs<T>& a, const TrackGeom<T>& g, c
 #pragma unroll
       for (int i = 0; i < 21; ++i) slot[(6 + i) * n] = c[i];
       slot[27 * n] = T(q);
-      if (j % f.seg != 0 && j + 1 < len - k0) {
+      if (j % f.seg != 0 && j + 1 < len - k0 && known_layer(g, lay)) {
         T m[3], V[6];
 #pragma unroll
         for (int x = 0; x < 3; ++x) m[x] = sb.v[x][jj][lane];

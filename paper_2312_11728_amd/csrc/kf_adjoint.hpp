@@ -515,6 +515,13 @@ KF_HD inline void state_before(const AdjArgs<T>& a, const TrackGeom<T>& g, const
   }
 }
 
+// A bad layer id stops the forward fit.  The refill, which does not know where
+// a fit stopped, leaves the state as it is there: no later one is read.
+template <typename T>
+KF_HD inline bool known_layer(const TrackGeom<T>& g, int lay) {
+  return lay >= 0 && lay < g.n_layers;
+}
+
 // With a state buffer: the states before entries js .. jhi (relative to the
 // first valid entry k0, 1 <= js <= jhi) of track t, recomputed from the
 // checkpoint of their segment in one pass and stored in slots js - 1 ..
@@ -538,9 +545,11 @@ KF_HD inline void fill_segment(const AdjArgs<T>& a, const TrackGeom<T>& g, const
     bool valid;
     T m[3], V[6];
     acc.load(k0 + j, lay, valid, m, V);
-    T c2;
-    uint32_t sst = 0;
-    step_forward(p, c, q, j, lay, prev, valid, m, V, g, sal, c2, sst);
+    if (known_layer(g, lay)) {
+      T c2;
+      uint32_t sst = 0;
+      step_forward(p, c, q, j, lay, prev, valid, m, V, g, sal, c2, sst);
+    }
     prev = lay;
   }
 }

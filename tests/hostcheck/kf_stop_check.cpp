@@ -4,10 +4,13 @@
 //   done  steps_done() counts the entries that the forward fit completed, for
 //         layers whose radius lies between those that the fit's state and the
 //         6x6 step's state of the same track reach.
+//   layer the refill of a track with a bad layer id reads no layer that is not
+//         there (under the address sanitizer).
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <random>
+#include <vector>
 
 #include "kf_adjoint.hpp"
 
@@ -165,10 +168,59 @@ int completed_entries() {
   return bad || edge < 100;
 }
 
+int bad_layer() {
+  constexpr int n_lay = 6, n_ent = 8, seg = 3, n_seg = (n_ent - 1 + seg - 1) / seg;
+  const std::vector<int32_t> kind(n_lay, 0);
+  const std::vector<double> pos{4, 8, 12, 16, 20, 24}, x0(n_lay, 0.02);
+  const kf::TrackGeom<double> g{kind.data(), pos.data(), x0.data(), n_lay, kBz, kMass};
+  const double seed[6] = {4, 0, 1, 0.5, 0.1, 1.2};
+  double sc[21] = {};
+  for (int i = 0; i < 6; ++i) sc[kf::sym(i, i)] = 1e-4;
+  const int8_t q = 1;
+  const int32_t off[2] = {0, n_ent};
+  for (int bad : {-1, n_lay}) {
+    std::vector<int16_t> layer{0, 1, 2, 3, 4, int16_t(bad), 5, 5};
+    std::vector<uint8_t> valid(n_ent, 1);
+    std::vector<double> hit(3 * n_ent), V(6 * n_ent, 0.0), ckpt(28 * n_seg), buf(size_t(n_ent - 1) * kf::kSegVals);
+    for (int k = 0; k < n_ent; ++k) {
+      hit[k] = 4.0 + 4.0 * k;
+      hit[n_ent + k] = 0.1 * k;
+      hit[2 * n_ent + k] = 1.0 + k;
+      V[k] = V[2 * n_ent + k] = V[5 * n_ent + k] = 1e-4;
+    }
+    for (int s = 0; s < n_seg; ++s) {   // any states will do
+      for (int i = 0; i < 6; ++i) ckpt[i * n_seg + s] = seed[i];
+      for (int i = 0; i < 21; ++i) ckpt[(6 + i) * n_seg + s] = sc[i];
+      ckpt[27 * n_seg + s] = 1.0;
+    }
+    kf::AdjArgs<double> r{};
+    r.f.n = r.f.ld = 1;
+    r.f.n_hits = n_ent;
+    r.f.max_len = n_ent;
+    r.f.seed_state = seed;
+    r.f.seed_cov = sc;
+    r.f.seed_charge = &q;
+    r.f.hit_offsets = off;
+    r.f.hit_layer = layer.data();
+    r.f.hit_valid = valid.data();
+    r.f.hit_pos = hit.data();
+    r.f.hit_cov = V.data();
+    r.f.ckpt = ckpt.data();
+    r.f.seg = seg;
+    r.f.n_seg = n_seg;
+    r.seg_buf = buf.data();
+    const kf::CsrTrack<double> acc{r.f, 0};
+    kf::refill_track(r, g, static_cast<const double*>(nullptr), 0, acc, n_ent);
+  }
+  std::printf("layer: read\n");
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   if (argc == 2 && !std::strcmp(argv[1], "step")) return unreachable_step<float>() | unreachable_step<double>();
   if (argc == 2 && !std::strcmp(argv[1], "done")) return completed_entries();
+  if (argc == 2 && !std::strcmp(argv[1], "layer")) return bad_layer();
   return 2;
 }

@@ -1,5 +1,5 @@
-"""The reverse sweep where a track's crossing is on the edge of existing, in a
-host build of the device code."""
+"""The reverse sweep of tracks that the forward fit stopped, or whose crossing is
+on the edge of existing, in a host build of the device code."""
 import os
 import subprocess
 
@@ -20,7 +20,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["step", "done"])
+@pytest.mark.parametrize("check", ["step", "done", "layer"])
 def test_stops(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr[-2000:]
