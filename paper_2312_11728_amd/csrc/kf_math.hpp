@@ -276,8 +276,11 @@ KF_HD inline void helix_nudge(HelixPt<T>& o, T w, T cot, T ds) {
   o.sphm = sp + dphi * cp;
   o.cphm = cp - dphi * sp;
   const T dh = T(0.5) * dphi;
-  // d sinc(h) / dh = (cos h - sinc h) / h, = -h/3 to O(h^3) near 0
-  const T dshc = k_abs(h) < T(0.05) ? -h * T(1.0 / 3.0) : (o.ch - o.shc) * k_rcp(h);
+  // d sinc(h) / dh = (cos h - sinc h) / h, near 0 its series to the digits that
+  // a dh below sqrt(0.01 eps) can move
+  T near0 = T(1.0 / 3.0);
+  if constexpr (sizeof(T) == 8) near0 = T(1.0 / 3.0) - h * h * (T(1.0 / 30.0) - h * h * T(1.0 / 840.0));
+  const T dshc = k_abs(h) < T(0.05) ? -h * near0 : (o.ch - o.shc) * k_rcp(h);
   const T sh = o.sh, ch = o.ch, sm = o.smid, cm = o.cmid;
   o.sh = sh + dh * ch;
   o.ch = ch - dh * sh;

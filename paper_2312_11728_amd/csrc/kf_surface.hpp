@@ -252,7 +252,8 @@ KF_HD inline bool cross_surface(const T p[6], T sphi, T cphi, T cot, T w, int ki
   }
   // Newton steps on r(s)^2 - R^2, two as in crossing().  A correction ds
   // whose dropped terms, (w ds)^2 and |w| ds^2 against R, stay below a
-  // hundredth of an ulp moves the point to first order; one within the
+  // hundredth of an ulp moves the point to first order (on turns of up to one
+  // radian, where the series below has all its digits); one within the
   // rounding of r^2 itself, |ds| <= 2 ulp(R), ends the search.
   cross_eval(p, sphi, cphi, cot, w, s, o);
   constexpr T eps = T(2.220446e-16);
@@ -264,8 +265,8 @@ KF_HD inline bool cross_surface(const T p[6], T sphi, T cphi, T cot, T w, int ki
     if (!(k_abs(df) > T(1e-20))) break;
     const T ds = -f * s_rcp(df);
     const T wd = w * ds;
-    if (wd * wd <= tiny && k_abs(w) * ds * ds <= tiny * pos) {
-      const T h = T(0.5) * o.u;
+    const T h = T(0.5) * o.u;
+    if (wd * wd <= tiny && k_abs(w) * ds * ds <= tiny * pos && k_abs(h) <= T(0.5)) {
       o.s += ds;
       o.x += ds * o.cphm;
       o.y += ds * o.sphm;
@@ -276,7 +277,8 @@ KF_HD inline bool cross_surface(const T p[6], T sphi, T cphi, T cot, T w, int ki
       const T sp = o.sphm, cp = o.cphm;
       o.sphm = sp + wd * cp;
       o.cphm = cp - wd * sp;
-      // d sinc(h) / dh = -h / 3 (1 - h^2 / 10 + h^4 / 280 - ...); wd is tiny
+      // d sinc(h) / dh = -h / 3 (1 - h^2 / 10 + h^4 / 280 - ...), whose next
+      // term, h^7 / 45360, moves less than an ulp for these h and wd
       const T h2 = h * h;
       o.shc -= T(0.5) * wd * h * (T(1.0 / 3.0) - h2 * (T(1.0 / 30.0) - h2 * T(1.0 / 840.0)));
     } else {
