@@ -3,6 +3,7 @@
 // per-track arrays are structure-of-arrays so that a wave's 64 lanes read and
 // write contiguous memory.
 #include "kf_kernels.hpp"
+#include "kf_order.hpp"
 #include "kf_stage.hpp"
 #include "kf_track.hpp"
 
@@ -218,26 +219,6 @@ __device__ void fit_wave_staged(const FitArgs<T>& a, const TrackGeom<T>& g, cons
   }
 }
 
-// Tracks per group of the length-sorted orders, and the block that runs a
-// group's part.  Within a group the tracks of a wave lie close together: they
-// share the cache lines of their hits and results, if the group's waves run at
-// the same time and behind one L2.  Blocks go to the kXcds dies in turn, so
-// the blocks of kXcds groups are dealt out in turn too: block r of them to
-// group r % kXcds (a permutation of the blocks; a last incomplete set of
-// groups keeps its order).  500k tracks of 3 to 26 entries, FP32: 333 us, from
-// 451 sorted as a whole (1.0 GB fetched, from 2.4, for 250 MB of hits).  Groups
-// of 8192 take as long.
-constexpr int kOrderGroup = 2048;
-constexpr int kXcds = 8;
-
-__device__ __forceinline__ int64_t run_order(int64_t block, int64_t n_blocks, int threads) {
-  const int per = kOrderGroup / threads;   // blocks per group
-  const int64_t set = block / (kXcds * per);
-  if ((set + 1) * (kXcds * per) > n_blocks) return block;
-  const int r = int(block - set * (kXcds * per));
-  return (set * kXcds + r % kXcds) * per + r / kXcds;
-}
-
 template <typename T, int WAVES, bool SORTED, int R2 = kFuseX>
 __global__ void __launch_bounds__(kFitBlock, WAVES) fit_staged_kernel(FitArgs<T> a, GeomArgs g) {
   constexpr int J = stage_entries<T, WAVES>();
@@ -247,8 +228,7 @@ __global__ void __launch_bounds__(kFitBlock, WAVES) fit_staged_kernel(FitArgs<T>
   __shared__ StageBuf<T, J> sb[kFitBlock / 64];
   stage_align(sal, a, g);
   stage_geometry(sg, g);
-  const int64_t block = SORTED ? run_order(blockIdx.x, gridDim.x, int(blockDim.x)) : int64_t(blockIdx.x);
-  const int64_t w0 = block * blockDim.x + (threadIdx.x & ~63u);
+  const int64_t w0 = int64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63u);
   fit_wave_staged<T, J, SORTED, R2>(a, TrackGeom<T>{sg.kind, sg.pos, sg.x0, g.n_layers, T(g.bz), T(g.mass)},
                                 a.align ? sal : nullptr, w0, sb[threadIdx.x >> 6], bk + threadIdx.x,
                                 int(blockDim.x));
@@ -282,7 +262,7 @@ __global__ void reset_counter_kernel(int32_t* c) { *c = 0; }
 // ---- length-sorted orders ------------------------------------------------------
 //
 // Layout 4: tracks sorted by length within groups of kOrderGroup consecutive
-// ones (order_group_kernel, run_order).  Layouts 1 and 2: all tracks, which
+// ones (order_group_kernel).  Layouts 1 and 2: all tracks, which
 // layout 2's packed copy of the hits needs; layout 1, whose lanes read their
 // hits one by one, gains nothing from neighbouring tracks (500k tracks: 1110
 // us sorted as a whole, 1253 in groups).
@@ -407,13 +387,14 @@ __global__ void __launch_bounds__(kSortBlock) length_scatter_kernel(const int32_
 }
 
 
-// Slots of layout 4, one block per group of tracks: longest first within
-// the group.  The order of tracks of equal length depends on scheduling; no
+// Slots of layout 4, one block per group of tracks: longest first within the
+// group, its waves where wave_place() says; a last incomplete group comes after
+// all others.  The order of tracks of equal length depends on scheduling; no
 // result does.
 constexpr int kOrderPer = kOrderGroup / kSortBlock;
 
 __global__ void __launch_bounds__(kSortBlock) order_group_kernel(const int32_t* off, int64_t n, int32_t max_len,
-                                                                 int32_t* order) {
+                                                                 int per_block, int32_t* order) {
   __shared__ int32_t at[kMaxLen + 1];   // tracks per length, then their next slots
   for (int i = threadIdx.x; i <= kMaxLen; i += kSortBlock) at[i] = 0;
   __syncthreads();
@@ -441,9 +422,15 @@ __global__ void __launch_bounds__(kSortBlock) order_group_kernel(const int32_t* 
     if (l == 63) at[0] = sum;
   }
   __syncthreads();
+  const int64_t n_groups = n / kOrderGroup;
 #pragma unroll
-  for (int k = 0; k < kOrderPer; ++k)
-    if (len[k] >= 0) order[b0 + atomicAdd(&at[len[k]], 1)] = int32_t(b0 + k * kSortBlock + threadIdx.x);
+  for (int k = 0; k < kOrderPer; ++k) {
+    if (len[k] < 0) continue;
+    const int i = atomicAdd(&at[len[k]], 1);
+    const int64_t wave = blockIdx.x < n_groups ? wave_place(blockIdx.x, i >> 6, n_groups, per_block)
+                                               : n_groups * kGroupWaves + (i >> 6);
+    order[wave * 64 + (i & 63)] = int32_t(b0 + k * kSortBlock + threadIdx.x);
+  }
 }
 
 // Fill the packed layout, one block per tile, through an LDS transpose: the
@@ -539,7 +526,8 @@ __global__ void __launch_bounds__(kPackBlock) pack_kernel(const int32_t* off, co
 }
 
 template <typename T>
-hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, PackedHits<T>* out, hipStream_t s) {
+hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const FitLaunch& l, PackedHits<T>* out,
+                       hipStream_t s) {
   const int nh = kMaxLen + 2;
   out->order = w.order;
   out->tile_base = nullptr;
@@ -548,7 +536,7 @@ hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, Packe
   out->stride = 0;
   if (layout == 4) {
     hipLaunchKernelGGL(order_group_kernel, dim3(unsigned((a.n + kOrderGroup - 1) / kOrderGroup)), dim3(kSortBlock), 0, s,
-                       a.hit_offsets, a.n, a.max_len, w.order);
+                       a.hit_offsets, a.n, a.max_len, l.persistent ? 0 : l.block / 64, w.order);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(128), 0, s, w.hist, nh);
@@ -642,7 +630,7 @@ template hipError_t launch_update<float>(const UpdArgs<float>&, hipStream_t);
 template hipError_t launch_update<double>(const UpdArgs<double>&, hipStream_t);
 template hipError_t launch_fit<float>(const FitArgs<float>&, const GeomArgs&, const FitLaunch&, int, hipStream_t);
 template hipError_t launch_fit<double>(const FitArgs<double>&, const GeomArgs&, const FitLaunch&, int, hipStream_t);
-template hipError_t launch_pack<float>(const FitArgs<float>&, const PackWork&, int, PackedHits<float>*, hipStream_t);
-template hipError_t launch_pack<double>(const FitArgs<double>&, const PackWork&, int, PackedHits<double>*, hipStream_t);
+template hipError_t launch_pack<float>(const FitArgs<float>&, const PackWork&, int, const FitLaunch&, PackedHits<float>*, hipStream_t);
+template hipError_t launch_pack<double>(const FitArgs<double>&, const PackWork&, int, const FitLaunch&, PackedHits<double>*, hipStream_t);
 
 }  // namespace kf

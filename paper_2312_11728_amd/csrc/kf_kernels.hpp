@@ -126,9 +126,6 @@ struct PackWork {
 };
 constexpr int kMaxLen = 64;
 
-template <typename T>
-hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, PackedHits<T>* out, hipStream_t s);
-
 // Launch functions (defined in kf_kernels.hip).
 template <typename T>
 hipError_t launch_seeds(const SeedArgs<T>& a, hipStream_t s);
@@ -148,6 +145,11 @@ struct FitLaunch {
 };
 template <typename T>
 hipError_t launch_fit(const FitArgs<T>& a, const GeomArgs& g, const FitLaunch& l, int n_cu, hipStream_t s);
+
+// The order, and for layout 2 the packed hits, of a fit that runs as l says.
+template <typename T>
+hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const FitLaunch& l, PackedHits<T>* out,
+                       hipStream_t s);
 
 // Reverse pass of the fit (gradient of sum_t w_t chi2_t).
 template <typename T>
