@@ -427,7 +427,9 @@ KF_HD inline void add_q(T c[21], T ipt, T sth, T cot, T var) {
 // G C G^T + g v^T + v g^T + a g g^T with v = G C d and a = d^T C d, which
 // uses the sparsity of G and never forms F.  BARREL: d[2] = d[5] = 0 (the
 // crossing of a cylinder about z).  The products with elements that are zero
-// are left out everywhere; adding them changes no bit of a finite result.
+// are left out everywhere; adding them changes no bit of a finite result, for
+// every sum is a chain x + a b, which fuses in one way only, so that a track
+// gets the same bits from either form.
 template <bool BARREL, typename T>
 KF_HD inline void transport_cov(T c[21], const T d[6], T G03, T G04, T G13, T G14, T G25, T G43, T g0, T g1, T g2,
                                 T g4) {
