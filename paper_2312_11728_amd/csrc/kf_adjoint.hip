@@ -74,11 +74,7 @@ __device__ void adjoint_wave_staged(const AdjArgs<T>& a, const TrackGeom<T>& g, 
 #pragma unroll
   for (int i = 0; i < 21; ++i) cb[i] = 0.0;
   int q_after = 0;
-  // state before entry j: slot j - 1 of the buffer the refill pass wrote, or
-  // of the checkpoints
-  const int64_t st = a.seg_buf ? f.n : f.ld * int64_t(f.n_seg);
-  const int64_t slot_st = a.seg_buf ? kSegVals * f.n : f.ld;
-  const T* slots = (a.seg_buf ? a.seg_buf : f.ckpt) + t;
+  const StoredStates<T> stored(a, t);
   wave_sync();
   StageRows<J> rows;
   stage_rows(sb, rows);
@@ -95,19 +91,10 @@ __device__ void adjoint_wave_staged(const AdjArgs<T>& a, const TrackGeom<T>& g, 
       T p[6], c[21], m[3], V[6];
       int q, prev = lay;
       if (j >= 1) {
-        const T* slot = slots + int64_t(j - 1) * slot_st;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) p[i] = slot[i * st];
-#pragma unroll
-        for (int i = 0; i < 21; ++i) c[i] = slot[(6 + i) * st];
-        q = int(slot[27 * st]);
+        stored.before(j, p, c, q);
         prev = jj + 1 < J ? int16_t(sb.lv[jj + 1][lane] & 0xffff) : f.hit_layer[e_last - (j0 + jj) - 1];
       } else {
-#pragma unroll
-        for (int i = 0; i < 6; ++i) p[i] = f.seed_state[i * f.ld + t];
-#pragma unroll
-        for (int i = 0; i < 21; ++i) c[i] = f.seed_cov[i * f.ld + t];
-        q = f.seed_charge[t];
+        stored.seed(p, c, q);
       }
 #pragma unroll
       for (int x = 0; x < 3; ++x) m[x] = sb.v[x][jj][lane];

@@ -613,12 +613,45 @@ KF_HD inline void fitted_range(const Acc& acc, int len, int max_len, int& k0, in
   n_steps = len - k0;
 }
 
+// The states of track t where every one is stored: that entering entry j is in
+// slot j - 1 of the buffer the refill pass wrote, or (seg = 1) of the
+// checkpoints; for j = 0 it is the seed.
+template <typename T>
+struct StoredStates {
+  const FitArgs<T>& f;
+  const int64_t t, st, slot_st;
+  const T* const slots;
+  KF_HD inline StoredStates(const AdjArgs<T>& a, int64_t track)
+      : f(a.f),
+        t(track),
+        st(a.seg_buf ? a.f.n : a.f.ld * int64_t(a.f.n_seg)),
+        slot_st(a.seg_buf ? kSegVals * a.f.n : a.f.ld),
+        slots((a.seg_buf ? a.seg_buf : a.f.ckpt) + track) {}
+  KF_HD inline void before(int j, T p[6], T c[21], int& q) const {   // j >= 1
+    const T* slot = slots + int64_t(j - 1) * slot_st;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) p[i] = slot[i * st];
+#pragma unroll
+    for (int i = 0; i < 21; ++i) c[i] = slot[(6 + i) * st];
+    q = int(slot[27 * st]);
+  }
+  KF_HD inline void seed(T p[6], T c[21], int& q) const {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) p[i] = f.seed_state[i * f.ld + t];
+#pragma unroll
+    for (int i = 0; i < 21; ++i) c[i] = f.seed_cov[i * f.ld + t];
+    q = f.seed_charge[t];
+  }
+};
+
 // Reverse sweep over the n_done entries that the forward fit completed of
 // track t (len entries, the first at e0 of the hit arrays), read through
-// `acc`.  STORED: the state before every entry is in the state buffer or (seg
-// = 1) a checkpoint; else it is recomputed from its segment's checkpoint.  The
-// charge after the last completed entry is not needed: the adjoints that a
-// flip there would change sign of are zero.
+// `acc`.  STORED: the state before every entry is read (StoredStates); else it
+// is recomputed from its segment's checkpoint.  The stored form is for host
+// builds: the device kernel takes the same steps on the same states with the
+// wave's hits and their gradients going through LDS.  The charge after the last
+// completed entry is not needed: the adjoints that a flip there would change
+// sign of are zero.
 template <bool STORED, typename T, typename Acc>
 KF_HD inline void adjoint_sweep(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
                                 const Acc& acc, int len, int64_t e0, int k0, int n_done) {
@@ -643,6 +676,7 @@ KF_HD inline void adjoint_sweep(const AdjArgs<T>& a, const TrackGeom<T>& g, cons
   for (int i = 0; i < 21; ++i) cb[i] = 0.0;
   int q_after = 0;
   bool last = true;
+  const StoredStates<T> stored(a, t);
   for (int j = n_done - 1; j >= 0; --j) {
     T p[6], c[21];
     int q, prev;
@@ -650,23 +684,14 @@ KF_HD inline void adjoint_sweep(const AdjArgs<T>& a, const TrackGeom<T>& g, cons
     bool valid;
     T m[3], V[6];
     acc.load(k0 + j, lay, valid, m, V);
-    if (STORED && j >= 1) {
-      // slot j - 1 of the buffer the refill pass wrote, or of the checkpoints
-      const int64_t st = a.seg_buf ? f.n : ld * int64_t(f.n_seg);
-      const T* slot = a.seg_buf ? a.seg_buf + int64_t(j - 1) * kSegVals * f.n + t : f.ckpt + int64_t(j - 1) * ld + t;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) p[i] = slot[i * st];
-#pragma unroll
-      for (int i = 0; i < 21; ++i) c[i] = slot[(6 + i) * st];
-      q = int(slot[27 * st]);
-      prev = acc.layer(k0 + j - 1);
-    } else if (STORED) {
-#pragma unroll
-      for (int i = 0; i < 6; ++i) p[i] = f.seed_state[i * ld + t];
-#pragma unroll
-      for (int i = 0; i < 21; ++i) c[i] = f.seed_cov[i * ld + t];
-      q = f.seed_charge[t];
-      prev = lay;
+    if constexpr (STORED) {
+      if (j >= 1) {
+        stored.before(j, p, c, q);
+        prev = acc.layer(k0 + j - 1);
+      } else {
+        stored.seed(p, c, q);
+        prev = lay;
+      }
     } else {
       state_before(a, g, sal, t, acc, k0, j, p, c, q, prev);
       if (j == 0) prev = lay;
@@ -681,15 +706,15 @@ KF_HD inline void adjoint_sweep(const AdjArgs<T>& a, const TrackGeom<T>& g, cons
   for (int i = 0; i < 6; ++i) a.grad_seed[i * ld + t] = T(pb[i]);
 }
 
-// Reverse pass of track t: the per-track form (host builds, and the device
-// kernel without a state buffer).
+// Reverse pass of track t, for host builds: what the device's stop kernel and
+// its sweep do to the track.
 template <typename T, typename Acc>
 KF_HD inline void adjoint_track(const AdjArgs<T>& a, const TrackGeom<T>& g, const T* __restrict__ sal, int64_t t,
                                 const Acc& acc, int len, int64_t e0) {
   int k0, n;
   fitted_range(acc, len, a.f.max_len, k0, n);
   if (n > 0 && was_stopped(a, t)) n = steps_done(a, g, sal, t, acc, k0, n);
-  if (a.seg_buf)
+  if (a.seg_buf || a.f.seg == 1)
     adjoint_sweep<true>(a, g, sal, t, acc, len, e0, k0, n);
   else
     adjoint_sweep<false>(a, g, sal, t, acc, len, e0, k0, n);
