@@ -408,6 +408,7 @@ __global__ void __launch_bounds__(kSortBlock) order_group_kernel(const int32_t* 
     if (len[k] >= 0) atomicAdd(&at[len[k]], 1);
   }
   __syncthreads();
+  static_assert(kMaxLen == 64, "one lane per length");
   if (threadIdx.x < 64) {
     // lane l holds the lengths kMaxLen - l, so that an inclusive scan over the
     // lanes counts the longer tracks; length 0 comes after all of them
