@@ -332,7 +332,7 @@ int kf_smooth_tracks(kf_ctx *ctx, kf_precision prec, int64_t n, int64_t ld,
  * pass did not refit it: there is no estimate from its other hits).  Entries outside the n tracks'
  * ranges are not written.
  * The rounds run on a context-owned workspace (about (34 + 55 * max_len)
- * values of the precision and 40 bytes per track, 10 values and 4 bytes per
+ * values of the precision and 32 bytes per track, 9 values and 4 bytes per
  * hit; grown on demand, KF_ERR_NOMEM if that fails).  At most max_reject + 1
  * rounds: the first runs on all n tracks; after each round the tracks still
  * open are gathered (their hits with them) into a compact sub-batch that the
@@ -437,8 +437,9 @@ typedef struct {
  * ids, which must be distinct, are what the output reports and what breaks
  * ties), pool_module[n_pool] (device, the detector module of each hit; may
  * be NULL when params->overlap is 0).  The call bins the pool by (layer, phi, z) into a context-owned
- * workspace (about 64 bytes per pool hit and 9 bytes per candidate slot and plan layer; grown on
- * demand, KF_ERR_NOMEM if that fails), unless params->reuse_bins allows the
+ * workspace (about 56 bytes per pool hit, and the larger of another 48 per
+ * pool hit, for pools of up to 2^25 hits, and 9 bytes per candidate slot and
+ * plan layer; grown on demand, KF_ERR_NOMEM if that fails), unless params->reuse_bins allows the
  * bins of the previous call to be used.  The per-layer parameters of the
  * plan are copied from host memory into that workspace on `stream` (a
  * host-to-device copy, synchronous with respect to the host) before the
@@ -483,8 +484,8 @@ int kf_score_hits(kf_ctx *ctx, int64_t n, int64_t ld,
  * align NULL it is the gradient at zero offsets).
  * trk_status[n]: the status kf_fit_tracks returned; tracks it stopped
  * (NO_CROSSING, NONFINITE, bad layer id) contribute only up to the entry
- * where they stopped.  Uses a context-owned buffer of 2 * 64 * ceil(n / 64)
- * values for the alignment reduction and, for seg > 1, n * (max_len - 1) * 29
+ * where they stopped.  Uses a context-owned buffer of 128 * ceil(n_hits / 2048)
+ * values for the alignment reduction and, for seg > 1, n * (max_len - 1) * 28
  * values into which a pass before the reverse sweep recomputes the state
  * before every entry, each checkpoint segment once from its checkpoint
  * (allocated on first need, grown on demand, KF_ERR_NOMEM if that fails);
