@@ -15,8 +15,8 @@
 //
 // FP32, 500k tracks, the whole call (us), sorted as a whole / in groups dealt
 // out in sets of eight without a front / this: lengths 3 to 15 474 / 329 / 317,
-// 3 to 26 with 1% at 26 492 / 557 / 421, nine of ten cut to 8 entries 272 / 433
-// / 266.  Two or four waves of each group in front: 322 and 331, 422 and 423,
+// 3 to 26 with 1% at 26 492 / 557 / 418, nine of ten cut to 8 entries 268 / 432
+// / 263.  Two or four waves of each group in front: 322 and 331, 422 and 423,
 // 263 and 261; none: 312, 478, 349.  Persistent blocks take their tiles as
 // they come, not in turn, and run the waves in line: 492 / 394 / 414, 516 / 509
 // / 484, 276 / 338 / 282.
