@@ -276,11 +276,16 @@ KF_HD inline void helix_nudge(HelixPt<T>& o, T w, T cot, T ds) {
   o.sphm = sp + dphi * cp;
   o.cphm = cp - dphi * sp;
   const T dh = T(0.5) * dphi;
-  // d sinc(h) / dh = (cos h - sinc h) / h, near 0 its series to the digits that
-  // a dh below sqrt(0.01 eps) can move
-  T near0 = T(1.0 / 3.0);
-  if constexpr (sizeof(T) == 8) near0 = T(1.0 / 3.0) - h * h * (T(1.0 / 30.0) - h * h * T(1.0 / 840.0));
-  const T dshc = k_abs(h) < T(0.05) ? -h * near0 : (o.ch - o.shc) * k_rcp(h);
+  T dshc;   // d sinc(h) / dh
+  if constexpr (sizeof(T) == 8) {
+    // -h / 3 (1 - h^2 / 10 + h^4 / 280 - ...), whose next term, h^7 / 45360,
+    // moves less than an ulp for |h| <= 0.5 and (w ds)^2 <= 0.01 ulp
+    const T h2 = h * h;
+    dshc = -h * (T(1.0 / 3.0) - h2 * (T(1.0 / 30.0) - h2 * T(1.0 / 840.0)));
+  } else {
+    // (cos h - sinc h) / h, = -h/3 to O(h^3) near 0
+    dshc = k_abs(h) < T(0.05) ? -h * T(1.0 / 3.0) : (o.ch - o.shc) * k_rcp(h);
+  }
   const T sh = o.sh, ch = o.ch, sm = o.smid, cm = o.cmid;
   o.sh = sh + dh * ch;
   o.ch = ch - dh * sh;
@@ -371,8 +376,8 @@ KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, b
   // tangency, where h'(s) is small and the closed-form root is least
   // accurate).  A correction whose second-order terms stay below a hundredth
   // of a unit in the last place, (w ds)^2 in the angles and |w| ds^2 against R
-  // in the position, moves the point to first order (helix_nudge); otherwise
-  // the point is evaluated afresh.
+  // in the position, moves the point to first order (helix_nudge; in FP64 on
+  // turns of up to one radian); otherwise the point is evaluated afresh.
   helix_eval(p, sphi, cphi, cot, w, best, hp);
   const T tiny = T(0.01 * (sizeof(T) == 4 ? 1.1920929e-7 : 2.220446e-16));
 #pragma unroll
@@ -383,7 +388,7 @@ KF_HD bool crossing(const T p[6], T sphi, T cphi, T cot, T w, int kind, T pos, b
       const T ds = -f * k_rcp(df);
       best += ds;
       const T wd = w * ds;
-      if (wd * wd <= tiny && k_abs(w) * ds * ds <= tiny * pos)
+      if (wd * wd <= tiny && k_abs(w) * ds * ds <= tiny * pos && (sizeof(T) == 4 || k_abs(hp.u) <= T(1)))
         helix_nudge(hp, w, cot, ds);
       else
         helix_eval(p, sphi, cphi, cot, w, best, hp);

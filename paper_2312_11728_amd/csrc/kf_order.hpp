@@ -26,7 +26,7 @@
 
 namespace kf {
 
-constexpr int kOrderGroup = 2048;   // (8192 take as long)
+constexpr int kOrderGroup = 2048;
 constexpr int kGroupWaves = kOrderGroup / 64;
 constexpr int kXcds = 8;
 
