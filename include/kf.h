@@ -181,7 +181,8 @@ int kf_update(kf_ctx *ctx, kf_precision prec, int64_t n, int64_t ld,
  * kf_reserve large enough for n tracks and max_len, the call can first sort
  * the tracks by entry count (longest first, so that the lanes of a wave run
  * similar loops; layout 4: within groups of 2048 consecutive tracks, the
- * longest 64 of every group first) and optionally copy the hits into a tile-transposed layout
+ * longest 64 of every group first in a batch beyond what the chip holds at
+ * once) and optionally copy the hits into a tile-transposed layout
  * (entry k of 64 tracks contiguous, every hit load of a wave one coalesced
  * read); the fit can also stage the CSR entries of each wave's 64 tracks
  * through LDS itself, a few entries per track at a time (no pass before the

@@ -382,7 +382,7 @@ template <typename T>
 hipError_t run_fit(kf_ctx* ctx, kf::FitArgs<T> a, const kf::GeomArgs& g, const kf::FitLaunch& l, int layout,
                    hipStream_t s, bool may_time = true) {
   if (layout == 1 || layout == 2 || layout == 4) {
-    hipError_t e = kf::launch_pack(a, ctx->work, layout, l, &a.pk, s);
+    hipError_t e = kf::launch_pack(a, ctx->work, layout, l, ctx->n_cu, &a.pk, s);
     if (e != hipSuccess) return e;
   }
   a.packed = layout;

@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(kSortBlock) length_scatter_kernel(const int32_
 constexpr int kOrderPer = kOrderGroup / kSortBlock;
 
 __global__ void __launch_bounds__(kSortBlock) order_group_kernel(const int32_t* off, int64_t n, int32_t max_len,
-                                                                 int per_block, int32_t* order) {
+                                                                 int per_block, int front, int32_t* order) {
   __shared__ int32_t at[kMaxLen + 1];   // tracks per length, then their next slots
   for (int i = threadIdx.x; i <= kMaxLen; i += kSortBlock) at[i] = 0;
   __syncthreads();
@@ -428,7 +428,7 @@ __global__ void __launch_bounds__(kSortBlock) order_group_kernel(const int32_t* 
   for (int k = 0; k < kOrderPer; ++k) {
     if (len[k] < 0) continue;
     const int i = atomicAdd(&at[len[k]], 1);
-    const int64_t wave = blockIdx.x < n_groups ? wave_place(blockIdx.x, i >> 6, n_groups, per_block)
+    const int64_t wave = blockIdx.x < n_groups ? wave_place(blockIdx.x, i >> 6, n_groups, per_block, front)
                                                : n_groups * kGroupWaves + (i >> 6);
     order[wave * 64 + (i & 63)] = int32_t(b0 + k * kSortBlock + threadIdx.x);
   }
@@ -527,8 +527,8 @@ __global__ void __launch_bounds__(kPackBlock) pack_kernel(const int32_t* off, co
 }
 
 template <typename T>
-hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const FitLaunch& l, PackedHits<T>* out,
-                       hipStream_t s) {
+hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const FitLaunch& l, int n_cu,
+                       PackedHits<T>* out, hipStream_t s) {
   const int nh = kMaxLen + 2;
   out->order = w.order;
   out->tile_base = nullptr;
@@ -536,8 +536,10 @@ hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const
   out->hit = nullptr;
   out->stride = 0;
   if (layout == 4) {
+    // a batch whose waves the chip holds all at once has no late blocks
+    const int front = (a.n + 63) / 64 > int64_t(n_cu) * 4 * l.waves ? 1 : 0;
     hipLaunchKernelGGL(order_group_kernel, dim3(unsigned((a.n + kOrderGroup - 1) / kOrderGroup)), dim3(kSortBlock), 0, s,
-                       a.hit_offsets, a.n, a.max_len, l.persistent ? 0 : l.block / 64, w.order);
+                       a.hit_offsets, a.n, a.max_len, l.persistent ? 0 : l.block / 64, front, w.order);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(128), 0, s, w.hist, nh);
@@ -631,7 +633,9 @@ template hipError_t launch_update<float>(const UpdArgs<float>&, hipStream_t);
 template hipError_t launch_update<double>(const UpdArgs<double>&, hipStream_t);
 template hipError_t launch_fit<float>(const FitArgs<float>&, const GeomArgs&, const FitLaunch&, int, hipStream_t);
 template hipError_t launch_fit<double>(const FitArgs<double>&, const GeomArgs&, const FitLaunch&, int, hipStream_t);
-template hipError_t launch_pack<float>(const FitArgs<float>&, const PackWork&, int, const FitLaunch&, PackedHits<float>*, hipStream_t);
-template hipError_t launch_pack<double>(const FitArgs<double>&, const PackWork&, int, const FitLaunch&, PackedHits<double>*, hipStream_t);
+template hipError_t launch_pack<float>(const FitArgs<float>&, const PackWork&, int, const FitLaunch&, int,
+                                        PackedHits<float>*, hipStream_t);
+template hipError_t launch_pack<double>(const FitArgs<double>&, const PackWork&, int, const FitLaunch&, int,
+                                         PackedHits<double>*, hipStream_t);
 
 }  // namespace kf

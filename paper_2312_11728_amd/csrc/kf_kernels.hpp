@@ -148,8 +148,8 @@ hipError_t launch_fit(const FitArgs<T>& a, const GeomArgs& g, const FitLaunch& l
 
 // The order, and for layout 2 the packed hits, of a fit that runs as l says.
 template <typename T>
-hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const FitLaunch& l, PackedHits<T>* out,
-                       hipStream_t s);
+hipError_t launch_pack(const FitArgs<T>& a, const PackWork& w, int layout, const FitLaunch& l, int n_cu,
+                       PackedHits<T>* out, hipStream_t s);
 
 // Reverse pass of the fit (gradient of sum_t w_t chi2_t).
 template <typename T>
